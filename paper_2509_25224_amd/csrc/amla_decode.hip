@@ -238,7 +238,8 @@ int enqueue_decode(const void* q, const void* kv_cache, const int32_t* block_tab
   if (balanced) {
     // (the row-rescale kernels leave their partial rows in FP16, the transposed-accumulator kernels in FP32)
     const auto combine = uses_transposed(desc) ? amla_combine_balanced_kernel<false> : amla_combine_balanced_kernel<true>;
-    hipLaunchKernelGGL(combine, dim3((unsigned)n_rows), dim3(128), 0, stream, p.part_o,
+    const size_t groups = ((size_t)p.rows + kMergeRows - 1) / kMergeRows;
+    hipLaunchKernelGGL(combine, dim3((unsigned)(desc->batch * groups)), dim3(64 * kMergeRows), 0, stream, p.part_o,
                        p.part_lse, p.seqlens, p.out, p.lse, p.batch, p.rows, ns, p.max_blocks);
     if (hipGetLastError() != hipSuccess) return AMLA_ERR_LAUNCH;
   } else if (ns > 1) {
@@ -361,9 +362,15 @@ int amla_plan_segments(const int32_t* seqlens, int32_t batch, int32_t workers, i
     total += plan_blocks_of(seqlens[b], kBlock);
   }
   if (total > (1ll << 31) - 1) return AMLA_ERR_UNSUPPORTED;
+  // (amla_decode has at most 256 workers; the kernels' arithmetic holds for any 16-bit number of them)
+  const bool narrow = workers <= 65535;
+  auto begin = [&](int w) { return narrow ? (long long)plan_range_begin(w, total, workers) : plan_worker_begin(w, total, workers); };
+  auto of_block = [&](long long g) {
+    return narrow ? (int32_t)plan_range_of_block((uint32_t)g, total, workers) : (int32_t)plan_worker_of_block(g, total, workers);
+  };
   int n = 0;
   for (int w = 0; w < workers; ++w) {
-    const long long g0 = plan_worker_begin(w, total, workers), g1 = plan_worker_begin(w + 1, total, workers);
+    const long long g0 = begin(w), g1 = begin(w + 1);
     if (g0 >= g1) continue;
     // the sequence that holds global block g0 (the kernel finds it with a wave-wide scan)
     long long base = 0;
@@ -385,8 +392,8 @@ int amla_plan_segments(const int32_t* seqlens, int32_t batch, int32_t workers, i
   long long before = 0;
   for (int b = 0; b < batch; ++b) {
     const int nb = plan_blocks_of(seqlens[b], kBlock);
-    seq_workers[2 * b] = nb > 0 ? (int32_t)plan_worker_of_block(before, total, workers) : -1;
-    seq_workers[2 * b + 1] = nb > 0 ? (int32_t)plan_worker_of_block(before + nb - 1, total, workers) : -1;
+    seq_workers[2 * b] = nb > 0 ? of_block(before) : -1;
+    seq_workers[2 * b + 1] = nb > 0 ? of_block(before + nb - 1) : -1;
     before += nb;
   }
   return n <= capacity ? AMLA_OK : AMLA_ERR_WORKSPACE;

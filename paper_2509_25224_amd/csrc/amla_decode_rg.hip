@@ -834,13 +834,10 @@ void amla_decode_rg_balanced_kernel(const DecodeParams p) {
 
   // total number of blocks of the batch, then this worker's range of the concatenated list
   int total = 0;
-  for (int c = 0; c < p.batch; c += 64) {
-    const int i = c + lane;
-    total += wave_sum(i < p.batch ? plan_blocks_of(plan_len(p.seqlens[i], p.max_blocks, kBlock), kBlock) : 0);
-  }
-  total = __builtin_amdgcn_readfirstlane(total);
-  const long long g0 = plan_worker_begin(stream, total, p.n_streams);
-  const long long g1 = plan_worker_begin(stream + 1, total, p.n_streams);
+  for (int i = lane; i < p.batch; i += 64) total += plan_blocks_of(plan_len(p.seqlens[i], p.max_blocks, kBlock), kBlock);
+  total = __builtin_amdgcn_readfirstlane(wave_sum(total));
+  const long long g0 = plan_range_begin(stream, total, p.n_streams);
+  const long long g1 = plan_range_begin(stream + 1, total, p.n_streams);
   if (g0 >= g1) return;
   // the sequence that holds global block g0, and g0's position in it
   int b0 = -1, jstart = 0, base = 0;

@@ -108,6 +108,7 @@ __device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
 // two FP32 values as a pair of FP16 (round to nearest even), lo in the low half
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ unsigned pack_f16(float lo, float hi) {
   f32x2 v = {lo, hi};
   f16x2 b = __builtin_convertvector(v, f16x2);
@@ -147,6 +148,12 @@ constexpr float kLazyThreshold = 8.f;   // base-2 units: the weights may grow to
 __device__ __forceinline__ int wave_sum(int v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
+
+__device__ __forceinline__ float wave_max(float v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
   return v;
 }
 

@@ -31,6 +31,15 @@ AMLA_PLAN_FN int64_t plan_worker_begin(int64_t w, int64_t T, int64_t W) { return
 // the worker whose range holds global block g, 0 <= g < T: the largest w with w T / W <= g
 AMLA_PLAN_FN int64_t plan_worker_of_block(int64_t g, int64_t T, int64_t W) { return ((g + 1) * W - 1) / T; }
 
+// The same two in the arithmetic a GPU has (no 64-bit integer division, which is over a hundred instructions
+// there), for W <= 65535 and T < 2^31: with T = q W + r, w T / W = w q + w r / W exactly; the quotient
+// ((g + 1) W - 1) / T < W is at least 1 / T > 2^-31 away from the next integer unless it is one, far more than a
+// double's rounding moves it.
+AMLA_PLAN_FN uint32_t plan_range_begin(uint32_t w, uint32_t T, uint32_t W) { return w * (T / W) + w * (T % W) / W; }
+AMLA_PLAN_FN uint32_t plan_range_of_block(uint32_t g, uint32_t T, uint32_t W) {
+  return (uint32_t)((double)((int64_t)(g + 1) * W - 1) / (double)T);
+}
+
 AMLA_PLAN_FN int32_t plan_blocks_of(int32_t kv_len, int32_t block) { return (kv_len + block - 1) / block; }
 
 // a length as the balanced kernels read it: inside the documented range [0, block * max_blocks] even

@@ -1,0 +1,21 @@
+"""The merge of partial rows where its passes and row groups have remainders: more than 64 pieces of a sequence (one lane
+each, several passes), more workers than blocks, row counts that no workgroup of four rows divides, more than 64
+sequences in the plan's sums, empty sequences.  The bounds are the ones of test_gpu_parity.py."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import check, env, run_gpu, to_dev  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+BALANCED, TRANSPOSED = 8, 128
+
+
+@pytest.mark.parametrize("flags", [BALANCED, BALANCED | TRANSPOSED], ids=["fp16", "fp32"])
+@pytest.mark.parametrize("heads,lens,workers", [(3, [9000], 130), (3, [4200], 200), (129, [4111, 70], 66),
+                                                (5, [0] + [260 + 9 * i for i in range(70)] + [0], 256)])
+def test_balanced_merge(env, flags, heads, lens, workers):
+    torch, orc, amla, wl = env
+    case = wl.make_case("merge", 81, batch=len(lens), s_q=1, heads=heads, seqlens=lens, spare_frac=0.1)
+    out, lse = run_gpu(torch, amla, case, to_dev(torch, case), variant=1, num_splits=workers, flags=flags)
+    want, want_lse = orc.decode(case.q_bits, case.kv_bits, case.block_table, case.seqlens, case.softmax_scale)
+    check(out, lse, want, want_lse, f"merge heads {heads} workers {workers} flags {flags}")
