@@ -34,6 +34,16 @@
 
 namespace {
 
+template <int N, class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl<N>(f, std::make_integer_sequence<int, N>{});
+}
+
 // LDS tile of these kernels, two regions.
 //   Region A, the first 64 16-byte chunks of every row (the 512 value columns; K and V operands): 64 rows of 68
 //   chunks (64 of data, 4 unused), the chunks of a row permuted within aligned groups of four: chunk c of row r
@@ -55,6 +65,17 @@ constexpr int kRgTileBytes = kRgRegionA + kBlock * kRgRowB;   // 77824 = 76 KiB
 constexpr int kRgLoadsA = kBlock / 4;                 // per wave: rows wave, wave + 4, ...
 constexpr int kRgLoadsB = 2;                          // per wave: row groups wave and wave + 4
 constexpr int kRgLdsBytes = 2 * kRgTileBytes;         // double buffer, 155648 of the 163840 bytes
+
+// The epilogue's staging rows: 512 FP32 columns, 32 bytes apart more than that, so that the two rows a register holds (four
+// apart) fall into different halves of the 64 banks.
+constexpr int kRgStageRow = kDv * 4 + 32;
+static_assert(8 * kRgStageRow <= kRgTileBytes / 4, "a wave's staging rows fit its quarter of a tile buffer");
+// A wave's own LDS traffic is served in order; the compiler must not reorder it across this point.
+#ifndef AMLA_TARGET_HOOKS
+#define AMLA_WAVE_LDS_ORDER() asm volatile("" ::: "memory")
+#else
+#define AMLA_WAVE_LDS_ORDER() ((void)__builtin_amdgcn_readfirstlane(0))   // the lanes meet
+#endif
 
 // One 16-byte-per-lane direct-to-LDS load from scalar base + per-lane 32-bit offset (lane l lands at lds + 16 l,
 // lds wave-uniform), issued from inline assembly like AMLA_HIDDEN_LDS_LOAD and for the same reason.
@@ -127,10 +148,6 @@ __device__ __forceinline__ float max_over_halves(const float x) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 #endif
-
-__device__ __forceinline__ float lane_value(float x, int src_lane) {
-  return __int_as_float(__builtin_amdgcn_ds_bpermute(4 * src_lane, __float_as_int(x)));
-}
 
 // ---- the output accumulator: a register file of its own ------------------------------------------------------
 // The 32 x 512 FP32 accumulator of a wave is the wave's 256 AccVGPRs, addressed by name: tile dt (value columns
@@ -232,23 +249,36 @@ __device__ __forceinline__ void acc_exponent_lower_rows(const int n23) {
   int x0, x1, x2, x3, y0, y1, y2, y3;
   asm volatile(AMLA_ACC_EACH_FOUR(AMLA_ACC_LOWER_FOUR) : AMLA_ACC_X4, AMLA_ACC_Y4 : [f] "v"(n23), [i] "n"(I) : AMLA_ACC_ALL);
 }
+// Registers 4 G .. 4 G + 3 of all 16 tiles (this half-wave's four of rows 8 G .. 8 G + 7) to LDS: register e of tile dt to
+// at + e * STRIDE + 128 dt.  DS instructions take AccVGPRs as data, two a statement.
+#define AMLA_ACC_STAGE_PAIR(dt) "ds_write2_b32 %0, a[%1+" #dt "*16], a[%1+" #dt "*16+16] offset0:32*(" #dt "%%8) offset1:32*(" #dt "%%8)+32\n\t"
+template <int G, int STRIDE>
+__device__ __forceinline__ void acc_stage_rows(LDS_PTR(uint8_t) at) {
+  static_for<4>([&](auto ec) {
+    constexpr int e = ec.value;
+    const unsigned lo = (unsigned)(__UINTPTR_TYPE__)at + e * STRIDE, hi = lo + 1024;
+    asm volatile(AMLA_ACC_STAGE_PAIR(0) AMLA_ACC_STAGE_PAIR(2) AMLA_ACC_STAGE_PAIR(4) AMLA_ACC_STAGE_PAIR(6)
+                 : : "v"(lo), "n"(4 * G + e) : "memory");
+    asm volatile(AMLA_ACC_STAGE_PAIR(8) AMLA_ACC_STAGE_PAIR(10) AMLA_ACC_STAGE_PAIR(12) AMLA_ACC_STAGE_PAIR(14)
+                 : : "v"(hi), "n"(4 * G + e) : "memory");
+  });
+}
 __device__ __forceinline__ void acc_idle(void) { asm volatile("s_nop 7"); }
 // x stays where it is in the instruction stream, and nothing of the compiler's lives in an AccVGPR across this point
 // (between two statements that name the accumulator it would otherwise be free to put short-lived operands there)
 #define AMLA_PIN(x) asm volatile("" : "+v"(x) : : AMLA_ACC_ALL)
 // the kernel owns every AccVGPR from here on
 __device__ __forceinline__ void acc_claim(void) { asm volatile("" : : : AMLA_ACC_ALL); }
+#else
+template <int G, int STRIDE>
+__device__ __forceinline__ void acc_stage_rows(LDS_PTR(uint8_t) at) {
+  static_for<kDv / 32>([&](auto dtc) {
+    static_for<4>([&](auto ec) {
+      *(LDS_PTR(float))(at + ec.value * STRIDE + 128 * dtc.value) = acc_read<16 * dtc.value + 4 * G + ec.value>();
+    });
+  });
+}
 #endif
-
-template <int N, class F, int... I>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl<N>(f, std::make_integer_sequence<int, N>{});
-}
 
 // One piece of the decode loop: blocks [j0, j1) of sequence b for the 128 rows of row tile `tile`, one
 // softmax state per row, result written in final form (to_final) or as an FP32 partial row set starting at
@@ -730,45 +760,69 @@ __device__ __forceinline__ void decode_piece(const DecodeParams& p, LDS_PTR(uint
   }
 
   // ---- epilogue (the final division by the row sum of Algorithm 1 / Algorithm 2) ----
-  l_b16 += __shfl_xor(l_b16, 32);
-  l_f32 += __shfl_xor(l_f32, 32);
+  int ln = lane;
+  AMLA_OPAQUE(ln);   // what depends on the lane is computed anew: kept across the loop it would be spilled
+  l_b16 += __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (ln ^ 32), __float_as_int(l_b16)));
+  l_f32 += __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (ln ^ 32), __float_as_int(l_f32)));
   const float inv = l_b16 > 0.f ? 1.f / l_b16 : 0.f;
   const float lse = l_f32 > 0.f ? (ref + fast_log2(l_f32)) * 0.6931471805599453f : -INFINITY;
-  if (row < p.rows && h == 0) {
-    if (to_final) {
-      if (p.lse != nullptr) p.lse[grow] = lse;
-    } else {
-      p.part_lse[part_row0 + row] = lse;
-    }
+  const int row_w = tile * kRowsPerWg + wave * 32;   // the wave's first row
+  if (ln < 32 && row_w + ln < p.rows) {
+    if (!to_final)
+      (p.part_lse + part_row0 + row_w)[ln] = lse;
+    else if (p.lse != nullptr)
+      (p.lse + (size_t)b * p.rows + row_w)[ln] = lse;
   }
+  // The accumulator goes out through LDS, eight rows at a time: as it stands a lane holds one column of a row and a
+  // store would write two bytes a lane (256 store instructions for a wave's 32 rows); turned around, a row is two stores
+  // of eight bytes a lane.  The staging area lies in the tile buffer that is not the last block's: nobody reads that one
+  // since the barrier at the top of the last block, and each wave keeps to its own quarter.  One wave per SIMD issues an
+  // instruction in four to five cycles, so the epilogue is bound by their number: about 620 for 32 rows, of which the
+  // scaling and the conversions are 380; the accumulator goes to LDS straight from its AccVGPRs.  Against stores from the
+  // accumulator's own layout: 16 rows over 256 keys 19.6 -> 18.9 us a call, one sequence of 3001 keys 31.2 -> 29.8, 64
+  // sequences of 4096 keys 101.7 -> 99.5 (together with the merge, which reads the rows in column order).
+  LDS_PTR(uint8_t) stage = smem + ((j1 - j0) & 1) * kRgTileBytes + wave * (kRgTileBytes / 4);
   acc_idle();
   acc_idle();
   acc_idle();
-  static_for<16>([&](auto ic) {
-    constexpr int i = ic.value;
-    const int rw = 8 * (i >> 2) + 4 * h + (i & 3);          // row of register i within the wave
-    const float inv_i = lane_value(inv, rw);
-    const int row_i = tile * kRowsPerWg + wave * 32 + rw;
-    float o[kDv / 32];
-    static_for<kDv / 32>([&](auto dt) { o[dt.value] = acc_read<16 * dt.value + i>() * inv_i; });
-    if (row_i < p.rows) {
-      if (to_final) {
-        uint16_t* orow = p.out + ((size_t)b * p.rows + row_i) * kDv + l32;
+  auto emit = [&](uint16_t* const first_row, auto half) {
+    auto pack = [&](float x, float y) { return (int)(half.value ? pack_f16(x, y) : pack_bf16(x, y)); };
+    static_for<4>([&](auto gc) {
+      constexpr int g = gc.value;          // rows 8 g .. 8 g + 7 of the wave: registers 4 g .. 4 g + 3 of every tile
+      const int n = p.rows - row_w - 8 * g;   // rows that exist (wave-uniform)
+      if (n <= 0) return;
+      AMLA_WAVE_LDS_ORDER();
+      acc_stage_rows<g, kRgStageRow>(stage + 4 * (ln >> 5) * kRgStageRow + (ln & 31) * 4);
+      AMLA_WAVE_LDS_ORDER();
+      uint16_t* const orow = first_row + 8 * g * kDv;
+      auto read = [&](int r, int half_row) { return *(LDS_PTR(f32x4))(stage + r * kRgStageRow + 16 * ln + 1024 * half_row); };
+      auto write = [&](int r, const f32x4 a, const f32x4 c) {   // columns 4 ln .. + 3 and 256 + 4 ln .. + 3
+        const float f = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(inv), 8 * g + r));
+        reinterpret_cast<i32x2*>(orow + r * kDv)[ln] = i32x2{pack(a[0] * f, a[1] * f), pack(a[2] * f, a[3] * f)};
+        reinterpret_cast<i32x2*>(orow + r * kDv + 256)[ln] = i32x2{pack(c[0] * f, c[1] * f), pack(c[2] * f, c[3] * f)};
+      };
+      if (n >= 8) {
+        f32x4 a[8], c[8];
 #pragma unroll
-        for (int dt = 0; dt < kDv / 32; ++dt) orow[32 * dt] = (uint16_t)pack_bf16(o[dt], 0.f);
+        for (int r = 0; r < 8; ++r) {
+          a[r] = read(r, 0);
+          c[r] = read(r, 1);
+        }
+#pragma unroll
+        for (int r = 0; r < 8; ++r) write(r, a[r], c[r]);
       } else {
-        // a partial row goes out in FP16 (the values are normalised, so of the value rows' magnitude; the merge
-        // weights them in FP32), the lane's 16 columns side by side at position 16 l32: two 16-byte stores
-        // instead of sixteen, and half the bytes that the combine kernel reads back
-        unsigned hw[kDv / 64];
-#pragma unroll
-        for (int k = 0; k < kDv / 64; ++k) hw[k] = pack_f16(o[2 * k], o[2 * k + 1]);
-        i32x4* prow = reinterpret_cast<i32x4*>(reinterpret_cast<uint16_t*>(p.part_o) + (part_row0 + row_i) * kDv + 16 * l32);
-        prow[0] = i32x4{(int)hw[0], (int)hw[1], (int)hw[2], (int)hw[3]};
-        prow[1] = i32x4{(int)hw[4], (int)hw[5], (int)hw[6], (int)hw[7]};
+#pragma unroll 1
+        for (int r = 0; r < n; ++r) write(r, read(r, 0), read(r, 1));
       }
-    }
-  });
+    });
+  };
+  // a partial row goes out in FP16 (the values are normalised, so of the value rows' magnitude; the merge weights
+  // them in FP32)
+  if (to_final)
+    emit(p.out + ((size_t)b * p.rows + row_w) * kDv, std::false_type{});
+  else
+    emit(reinterpret_cast<uint16_t*>(p.part_o) + (part_row0 + row_w) * kDv, std::true_type{});
+  AMLA_WAVE_LDS_ORDER();
 }
 
 // Equal-share decomposition: workgroup = (sequence, split, 128-row tile).

@@ -64,7 +64,7 @@ struct DecodeParams {
   const int32_t* seqlens;   // [B]
   uint16_t* out;            // [B, G, 512] bf16 bits
   float* lse;               // [B, G] or null
-  float* part_o;            // [n_splits, B, G, 512] f32 (n_splits > 1)
+  float* part_o;            // [n_splits, B, G, 512] (n_splits > 1); FP16 rows from the row-rescale kernels, else FP32
   float* part_lse;          // [n_splits, B, G]
   float scale_log2e;        // softmax_scale * log2(e)
   int32_t batch;

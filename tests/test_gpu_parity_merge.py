@@ -19,3 +19,13 @@ def test_balanced_merge(env, flags, heads, lens, workers):
     out, lse = run_gpu(torch, amla, case, to_dev(torch, case), variant=1, num_splits=workers, flags=flags)
     want, want_lse = orc.decode(case.q_bits, case.kv_bits, case.block_table, case.seqlens, case.softmax_scale)
     check(out, lse, want, want_lse, f"merge heads {heads} workers {workers} flags {flags}")
+
+
+@pytest.mark.parametrize("flags", [0, TRANSPOSED], ids=["fp16", "fp32"])
+@pytest.mark.parametrize("heads,s_q,splits", [(3, 1, 100), (13, 1, 1), (21, 3, 9), (129, 1, 65), (128, 2, 8)])
+def test_equal_share_merge_and_row_remainders(env, flags, heads, s_q, splits):
+    torch, orc, amla, wl = env
+    case = wl.make_case("merge", 82, batch=3, s_q=s_q, heads=heads, seqlens=[9000, 300, 0], spare_frac=0.1)
+    out, lse = run_gpu(torch, amla, case, to_dev(torch, case), variant=1, num_splits=splits, flags=flags)
+    want, want_lse = orc.decode(case.q_bits, case.kv_bits, case.block_table, case.seqlens, case.softmax_scale)
+    check(out, lse, want, want_lse, f"merge heads {heads} s_q {s_q} splits {splits} flags {flags}")
