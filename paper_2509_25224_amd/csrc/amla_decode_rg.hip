@@ -66,14 +66,23 @@ constexpr int kRgLoadsA = kBlock / 4;                 // per wave: rows wave, wa
 constexpr int kRgLoadsB = 2;                          // per wave: row groups wave and wave + 4
 constexpr int kRgLdsBytes = 2 * kRgTileBytes;         // double buffer, 155648 of the 163840 bytes
 
+// Query rows on their way into registers: half a row (36 chunks) and one chunk more, so that 16 rows' chunks of one column
+// fall into distinct banks (37 is odd); a wave's 32 rows take 19 loads of one KiB.
+constexpr int kQStageRow = 37 * 16;
+constexpr int kQStageLoads = (32 * kQStageRow + 1023) / 1024;
+static_assert(kQStageLoads * 1024 <= kRgTileBytes / 4, "a wave's query rows fit its quarter of a tile buffer");
+
 // The epilogue's staging rows: 512 FP32 columns, 32 bytes apart more than that, so that the two rows a register holds (four
 // apart) fall into different halves of the 64 banks.
 constexpr int kRgStageRow = kDv * 4 + 32;
 static_assert(8 * kRgStageRow <= kRgTileBytes / 4, "a wave's staging rows fit its quarter of a tile buffer");
 // A wave's own LDS traffic is served in order; the compiler must not reorder it across this point.
+// AMLA_WAIT_LOADS_BUT(n): all but the last n direct-to-LDS loads of this wave have landed.
 #ifndef AMLA_TARGET_HOOKS
+#define AMLA_WAIT_LOADS_BUT(n) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(n) : "memory")
 #define AMLA_WAVE_LDS_ORDER() asm volatile("" ::: "memory")
 #else
+#define AMLA_WAIT_LOADS_BUT(n) wait_tile_loads_but(n)
 #define AMLA_WAVE_LDS_ORDER() ((void)__builtin_amdgcn_readfirstlane(0))   // the lanes meet
 #endif
 
@@ -294,9 +303,6 @@ __device__ __forceinline__ void decode_piece(const DecodeParams& p, LDS_PTR(uint
                                              const int entry = 0) {
   const int l32 = lane & 31;
   const int h = lane >> 5;
-  const int row = tile * kRowsPerWg + wave * 32 + l32;   // this lane's query row within the sequence
-  const size_t grow = (size_t)b * p.rows + (row < p.rows ? row : 0);
-
   float m_run = -INFINITY;   // running row max of t = s * scale * log2 e
   float ref = 0.f;           // reference subtracted in the exponent: m_run (MUL), rint(m_run) (ADD),
                              // m_run - log2 S16 (ADD_COMP)
@@ -357,31 +363,73 @@ __device__ __forceinline__ void decode_piece(const DecodeParams& p, LDS_PTR(uint
     return;
   }
 
-  // Q fragment: B operand of S^T = K Q^T.  Lane holds q[row][16 ks + 8 h .. + 7].  Rows past the end of the
-  // sequence's row range read row 0 (valid memory); their results are never stored.
-  bf16x8 qf[kDqk / 16];
-  const i32x4* qrow = reinterpret_cast<const i32x4*>(p.q + grow * kDqk) + h;
-#pragma unroll
-  for (int ks = 0; ks < kDqk / 16; ++ks) qf[ks] = __builtin_bit_cast(bf16x8, qrow[2 * ks]);
-  __builtin_amdgcn_sched_barrier(0);
   const int first_phys = min(max(__builtin_amdgcn_readfirstlane(first_entry), 0), p.num_blocks - 1);
 
   // the previous piece's last tile may still be read by a slower wave
   if (!first_piece) __syncthreads();
+
+  // Q fragment: B operand of S^T = K Q^T.  Lane holds q[row][16 ks + 8 h .. + 7].  A fragment's load from memory would
+  // touch 32 rows for 32 bytes each (36 of them took 5.3 us from the kernel's entry on, whatever the load on the memory
+  // system), so the rows come through LDS in whole lines, in two halves of 36 chunks: each wave through its own quarter of
+  // the second tile buffer, which the second tile enters only behind the first block's barrier; the first tile is on
+  // its way meanwhile.  (One sequence of 3001 keys 29.8 -> 28.0 us a call, 12 of up to 2100 37.8 -> 36.3.)  Chunks past
+  // the end of the sequence's row range repeat the last one (valid memory); the results of such rows are never stored.
+  const int row_w = tile * kRowsPerWg + wave * 32;   // the wave's first row
+  LDS_PTR(uint8_t) q_stage = smem + kRgTileBytes + wave * (kRgTileBytes / 4);
+  const uint8_t* q_base = reinterpret_cast<const uint8_t*>(p.q) + ((size_t)b * p.rows + row_w) * kRowBytes;
+  unsigned q_off[kQStageLoads];   // chunk 64 n + lane of the staged half: row (64 n + lane) / 37
+  {
+    const unsigned most = (unsigned)((min(32, p.rows - row_w) - 1) * kRowBytes + 36 * 16);
+    int ql = lane;
+    AMLA_OPAQUE(ql);   // (hoisted out of the loop over pieces, the 19 offsets would be spilled)
+    unsigned cc = ql < 37 ? ql : ql - 37;
+    unsigned off = (ql < 37 ? 0 : kRowBytes) + 16 * cc;
+#pragma unroll
+    for (int n = 0; n < kQStageLoads; ++n) {
+      q_off[n] = min(off, most);
+      const bool wrap = cc >= 37 - 27;   // 64 chunks on: one row and 27 chunks
+      off += kRowBytes + 27 * 16 + (wrap ? kRowBytes - 37 * 16 : 0);
+      cc = wrap ? cc - 10 : cc + 27;
+    }
+  }
+  // The odd chunk of a staged row is the one behind it for the first half, the one before it for the second.
+  auto load_queries = [&](auto half) {
+    static_for<kQStageLoads>([&](auto n) {
+      AMLA_HIDDEN_LDS_LOAD_AT(q_base, q_off[n.value], half.value * 35 * 16, q_stage, n.value * 1024);
+    });
+  };
+  bf16x8 qf[kDqk / 16];
+  auto read_queries = [&](auto half) {
+    AMLA_WAVE_LDS_ORDER();
+#pragma unroll
+    for (int ks = 0; ks < kDqk / 32; ++ks)
+      qf[half.value * (kDqk / 32) + ks] = *(LDS_PTR(bf16x8))(q_stage + l32 * kQStageRow + 16 * (2 * ks + h + half.value));
+#pragma unroll
+    for (int ks = 0; ks < kDqk / 32; ++ks) AMLA_ARRIVED(qf[half.value * (kDqk / 32) + ks]);
+    AMLA_WAVE_LDS_ORDER();
+  };
+  constexpr std::integral_constant<int, 0> first_half;
+  constexpr std::integral_constant<int, 1> second_half;
+  load_queries(first_half);
   const TileLoadLane tl = tile_load_lane(wave, lane);
-  if (j0 < j1 && fetch_own_share) {
+  const bool fetch_first = j0 < j1 && fetch_own_share;
+  if (fetch_first) {
     const uint8_t* first = kvb + (size_t)first_phys * blk_bytes;
     static_for<kRgLoadsPerWave>([&](auto k) { issue_tile_load<k.value>(first, smem, wave, tl); });
   }
 
-  // (The first tile and the query rows are on their way; the accumulator is cleared under their latency.)
+  // (The accumulator is cleared under the latency of these loads.)
   // accumulator register 16 dt + i: value column 32 dt + l32, query row 32 wave + 8 (i / 4) + 4 h + i % 4
   static_for<kDv / 32>([&](auto dt) { acc_clear_tile<dt.value>(); });
 
-  // The query rows are waited for here: the tile loads are hidden from the compiler's wait counting, and a wait
-  // for these loads left inside the loop would be a wait for the tile.
-#pragma unroll
-  for (int ks = 0; ks < kDqk / 16; ++ks) AMLA_ARRIVED(qf[ks]);
+  if (fetch_first)
+    AMLA_WAIT_LOADS_BUT(kRgLoadsPerWave);
+  else
+    AMLA_WAIT_LOADS_BUT(0);
+  read_queries(first_half);
+  load_queries(second_half);
+  AMLA_WAIT_LOADS_BUT(0);
+  read_queries(second_half);
 
   // per-lane LDS offsets of the operand reads (see the tile layout above)
   // [C1] A operand, steps 0 .. 31 (region A): row l32 (+ 32 for the second key tile), chunk 2 ks + h; even and
@@ -766,7 +814,6 @@ __device__ __forceinline__ void decode_piece(const DecodeParams& p, LDS_PTR(uint
   l_f32 += __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (ln ^ 32), __float_as_int(l_f32)));
   const float inv = l_b16 > 0.f ? 1.f / l_b16 : 0.f;
   const float lse = l_f32 > 0.f ? (ref + fast_log2(l_f32)) * 0.6931471805599453f : -INFINITY;
-  const int row_w = tile * kRowsPerWg + wave * 32;   // the wave's first row
   if (ln < 32 && row_w + ln < p.rows) {
     if (!to_final)
       (p.part_lse + part_row0 + row_w)[ln] = lse;
