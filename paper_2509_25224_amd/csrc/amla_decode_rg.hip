@@ -334,14 +334,22 @@ __device__ __forceinline__ void decode_piece(const DecodeParams& p, LDS_PTR(uint
   if (wave >= working_waves) {   // wave-uniform
     const int first_phys = min(max(__builtin_amdgcn_readfirstlane(first_entry), 0), p.num_blocks - 1);
     if (!first_piece) __syncthreads();
-    const TileLoadLane tl_even = tile_load_lane(0, lane), tl_odd = tile_load_lane(1, lane);
     const int fetchers = kThreads / 64 - working_waves, me = wave - working_waves;
+    // The 64 rows of region A and the 8 row groups of region B are dealt among the fetching waves, in plain loops: a
+    // kernel's code has to stay below the 64 KiB of the instruction cache (unrolled like the working waves' loads these
+    // are 8 KiB more, with which the small calls were 2 us slower).
+    const int chunk = lane & ~3, c8_even = (lane & 7) ^ (lane >> 4);
     auto fetch_tile = [&](const uint8_t* block, LDS_PTR(uint8_t) to) {
-      // load n of wave w's share is slot 4 n + w; a fetching wave takes the slots congruent to its number
-      static_for<kRgLoadsPerWave>([&](auto k) {
-        for (int w = 0; w < kThreads / 64; ++w)
-          if ((4 * k.value + w) % fetchers == me) issue_tile_load<k.value>(block, to, w, (w & 1) ? tl_odd : tl_even);
-      });
+#pragma unroll 1
+      for (int i = me; i < kBlock; i += fetchers) {
+        const unsigned off = 16u * (unsigned)(chunk | ((lane - (i >> 2)) & 3));
+        AMLA_HIDDEN_LDS_LOAD_AT(block + i * kRowBytes, off, 0, to + i * kRgRowA, 0);
+      }
+#pragma unroll 1
+      for (int m = me; m < kBlock / 8; m += fetchers) {
+        const unsigned off = (unsigned)((lane >> 3) * kRowBytes + 64 * 16 + 16 * (c8_even ^ (4 * (m & 1))));
+        AMLA_HIDDEN_LDS_LOAD_AT(block + m * 8 * kRowBytes, off, 0, to + m * 1024, kRgRegionA);
+      }
     };
     if (j0 < j1) fetch_tile(kvb + (size_t)first_phys * blk_bytes, smem);
     for (int j = j0; j < j1; ++j) {
