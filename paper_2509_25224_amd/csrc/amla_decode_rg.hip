@@ -880,7 +880,29 @@ __device__ __forceinline__ void decode_piece(const DecodeParams& p, LDS_PTR(uint
   AMLA_WAVE_LDS_ORDER();
 }
 
-// Equal-share decomposition: workgroup = (sequence, split, 128-row tile).
+// The sequence that holds global block g of the batch's blocks laid end to end (0 <= g < their number), and the block's
+// position in it.
+__device__ __forceinline__ void find_block(const DecodeParams& p, const int g, const int lane, int& b, int& j) {
+  int base = 0;
+  b = -1;
+  j = 0;
+  for (int c = 0; c < p.batch && b < 0; c += 64) {
+    const int i = c + lane;
+    const int nbi = i < p.batch ? plan_blocks_of(plan_len(p.seqlens[i], p.max_blocks, kBlock), kBlock) : 0;
+    const int incl = wave_inclusive_scan(nbi, lane);
+    const unsigned long long mask = __builtin_amdgcn_ballot_w64(g < base + incl);
+    if (mask != 0) {   // the first lane whose sequence ends behind g
+      const int l = __builtin_amdgcn_readfirstlane(__builtin_ctzll(mask));
+      b = c + l;
+      j = g - (base + __builtin_amdgcn_readlane(incl - nbi, l));
+    }
+    base += __builtin_amdgcn_readlane(incl, 63);
+  }
+}
+
+// Equal-share decomposition: workgroup = (sequence, split, 128-row tile).  Where the library chose the split factor
+// (p.n_workers > 0) the workgroups look at the lengths first and take the ranges of the balanced decomposition instead
+// if equal shares would wait for the longest sequence (plan_prefers_ranges; the merge decides by the same rule).
 template <int VARIANT, bool ITER512>
 __global__ __launch_bounds__(kThreads) AMLA_ONE_WAVE_PER_SIMD
 void amla_decode_rg_kernel(const DecodeParams p) {
@@ -899,23 +921,72 @@ void amla_decode_rg_kernel(const DecodeParams p) {
   const int slot = blockIdx.x >> 3;
   const int group = slot / p.n_tiles;
   const int tile = slot % p.n_tiles;
-  const int b = (group / p.n_splits) * 8 + xcd;
-  const int split = group % p.n_splits;
-  if (b >= p.batch) return;
+
+  // as a worker: neighbouring workers, which often share a sequence's query rows, on one XCD
+  const int per_xcd = (p.n_workers + 7) / 8;
+  const int worker = xcd * per_xcd + group;
+  int b = (group / p.n_splits) * 8 + xcd;
+  const bool there = b < p.batch;
 
   // The first 64 entries of the sequence's block-table row are asked for together with its length, one per lane:
   // a share that starts within them (any share of a sequence of up to 4096 keys, the first shares of a longer
-  // one) then has its first entry without a second memory round trip before the first tile can be requested.
-  const int32_t* table_row = p.table + (size_t)b * p.max_blocks;
-  const int lane_entry = table_row[min(lane, p.max_blocks - 1)];
-  const int kv_len = plan_len(__builtin_amdgcn_readfirstlane(p.seqlens[b]), p.max_blocks, kBlock);
-  const int nb = plan_blocks_of(kv_len, kBlock);
-  const int j0 = (int)(((long long)split * nb) / p.n_splits);
-  const int j1 = (int)(((long long)(split + 1) * nb) / p.n_splits);
-  const bool have_entry = j0 < 64;
-  const int entry = __builtin_amdgcn_readlane(lane_entry, j0 & 63);
-  decode_piece<VARIANT, false, ITER512>(p, smem, lane, wave, b, kv_len, j0, j1, tile, p.n_splits == 1,
-                               (size_t)split * p.batch * p.rows + (size_t)b * p.rows, 0, 0, true, have_entry, entry);
+  // one) then has its first entry without a second memory round trip before the first tile can be requested.  (Also
+  // before it is known whether ranges are the better choice.)
+  int lane_entry = 0, len = 0;
+  auto ask = [&]() {
+    lane_entry = (p.table + (size_t)b * p.max_blocks)[min(lane, p.max_blocks - 1)];
+    len = p.seqlens[b];
+  };
+  if (there) ask();
+
+  int g0 = 0, g1 = 0, j = 0;   // this worker's global blocks; none (g1 = 0) with equal shares
+  if (p.n_workers > 0) {
+    const BatchBlocks blocks = batch_blocks(p.seqlens, p.batch, p.max_blocks, 0, lane);
+    if (plan_prefers_ranges(blocks.total, blocks.longest, p.n_splits, p.n_workers, p.n_rounds)) {
+      if (group >= per_xcd || worker >= p.n_workers) return;
+      g0 = plan_range_begin(worker, blocks.total, p.n_workers);
+      g1 = plan_range_begin(worker + 1, blocks.total, p.n_workers);
+      if (g0 >= g1) return;
+      find_block(p, g0, lane, b, j);
+      if (b < 0) return;   // unreachable when g0 < total
+      ask();
+    }
+  }
+  if (g1 == 0 && !there) return;
+
+  bool first_piece = true;
+  for (;;) {
+    const int kv_len = plan_len(__builtin_amdgcn_readfirstlane(len), p.max_blocks, kBlock);
+    const int nb = plan_blocks_of(kv_len, kBlock);
+    const bool ranges = g1 > 0;
+    int j0, j1;
+    bool whole;
+    size_t part_row0;
+    if (ranges) {
+      j0 = j;
+      j1 = min(nb, j + (g1 - g0));
+      whole = j0 == 0 && j1 == nb;
+      part_row0 = (size_t)(worker + b) * p.rows;
+    } else {
+      const int split = group % p.n_splits;
+      j0 = (int)plan_range_begin(split, nb, p.n_splits);
+      j1 = (int)plan_range_begin(split + 1, nb, p.n_splits);
+      whole = p.n_splits == 1;
+      part_row0 = ((size_t)split * p.batch + b) * p.rows;
+    }
+    const bool have_entry = j0 < 64;
+    const int entry = __builtin_amdgcn_readlane(lane_entry, j0 & 63);
+    if (!ranges || j0 < j1) {   // (a range passes over sequences without blocks)
+      decode_piece<VARIANT, false, ITER512>(p, smem, lane, wave, b, kv_len, j0, j1, tile, whole, part_row0, 0, 0, first_piece,
+                                            have_entry, entry);
+      first_piece = false;
+    }
+    g0 += j1 - j0;
+    j = 0;
+    ++b;
+    if (g0 >= g1 || b >= p.batch) break;
+    ask();
+  }
 }
 
 // Balanced decomposition (ragged batches, causal mask among the s_q tokens, per-sequence query counts):
@@ -933,37 +1004,19 @@ void amla_decode_rg_balanced_kernel(const DecodeParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   acc_claim();
 
-  // workers go round-robin over the 8 XCDs; the row tiles of one worker sit next to each other on the same
-  // XCD and share the worker's KV blocks in that XCD's L2
-  const int xcd = blockIdx.x & 7;
-  const int slot = blockIdx.x >> 3;
-  const int stream = (slot / p.n_tiles) * 8 + xcd;
-  const int tile = slot % p.n_tiles;
-  if (stream >= p.n_streams) return;
+  // Workgroup ids go round-robin over the 8 XCDs: neighbouring workers, which often share a sequence's query rows, sit on
+  // one XCD, and so do the row tiles of a worker, which share its KV blocks in that XCD's L2.
+  const int per_xcd = (p.n_streams + 7) / 8;
+  const int stream = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3) / p.n_tiles;
+  const int tile = (blockIdx.x >> 3) % p.n_tiles;
+  if ((blockIdx.x >> 3) / p.n_tiles >= per_xcd || stream >= p.n_streams) return;
 
-  // total number of blocks of the batch, then this worker's range of the concatenated list
-  int total = 0;
-  for (int i = lane; i < p.batch; i += 64) total += plan_blocks_of(plan_len(p.seqlens[i], p.max_blocks, kBlock), kBlock);
-  total = __builtin_amdgcn_readfirstlane(wave_sum(total));
-  const long long g0 = plan_range_begin(stream, total, p.n_streams);
-  const long long g1 = plan_range_begin(stream + 1, total, p.n_streams);
+  // total number of blocks of the batch, this worker's range of the concatenated list, and where that starts
+  const int total = batch_blocks(p.seqlens, p.batch, p.max_blocks, 0, lane).total;
+  const int g0 = plan_range_begin(stream, total, p.n_streams), g1 = plan_range_begin(stream + 1, total, p.n_streams);
   if (g0 >= g1) return;
-  // the sequence that holds global block g0, and g0's position in it
-  int b0 = -1, jstart = 0, base = 0;
-  for (int c = 0; c < p.batch && b0 < 0; c += 64) {
-    const int i = c + lane;
-    const int nbi = i < p.batch ? plan_blocks_of(plan_len(p.seqlens[i], p.max_blocks, kBlock), kBlock) : 0;
-    const int incl = wave_inclusive_scan(nbi, lane);
-    const int excl = incl - nbi;
-    const bool hit = (long long)base + excl <= g0 && g0 < (long long)base + incl;
-    const unsigned long long mask = __builtin_amdgcn_ballot_w64(hit);
-    if (mask != 0) {
-      const int l = __builtin_amdgcn_readfirstlane(__builtin_ctzll(mask));
-      b0 = c + l;
-      jstart = (int)(g0 - ((long long)base + __builtin_amdgcn_readlane(excl, l)));
-    }
-    base += __builtin_amdgcn_readlane(incl, 63);
-  }
+  int b0, jstart;
+  find_block(p, g0, lane, b0, jstart);
   if (b0 < 0) return;   // unreachable when g0 < total
 
   const int row = tile * kRowsPerWg + wave * 32 + (lane & 31);   // this lane's query row within the sequence

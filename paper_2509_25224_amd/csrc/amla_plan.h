@@ -32,10 +32,13 @@ AMLA_PLAN_FN int64_t plan_worker_begin(int64_t w, int64_t T, int64_t W) { return
 AMLA_PLAN_FN int64_t plan_worker_of_block(int64_t g, int64_t T, int64_t W) { return ((g + 1) * W - 1) / T; }
 
 // The same two in the arithmetic a GPU has (no 64-bit integer division, which is over a hundred instructions
-// there), for W <= 65535 and T < 2^31: with T = q W + r, w T / W = w q + w r / W exactly; the quotient
+// there), for W <= 256 and T < 2^31: with T = q W + r, w T / W = w q + w r / W exactly, and w r < 2^16 is so small that a
+// float's product with 1 / W, half a step up, is never on the wrong side of an integer; the quotient
 // ((g + 1) W - 1) / T < W is at least 1 / T > 2^-31 away from the next integer unless it is one, far more than a
 // double's rounding moves it.
-AMLA_PLAN_FN uint32_t plan_range_begin(uint32_t w, uint32_t T, uint32_t W) { return w * (T / W) + w * (T % W) / W; }
+AMLA_PLAN_FN uint32_t plan_range_begin(uint32_t w, uint32_t T, uint32_t W) {
+  return w * (T / W) + (uint32_t)(((float)(w * (T % W)) + 0.5f) * (1.0f / (float)W));
+}
 AMLA_PLAN_FN uint32_t plan_range_of_block(uint32_t g, uint32_t T, uint32_t W) {
   return (uint32_t)((double)((int64_t)(g + 1) * W - 1) / (double)T);
 }
@@ -47,6 +50,19 @@ AMLA_PLAN_FN int32_t plan_blocks_of(int32_t kv_len, int32_t block) { return (kv_
 AMLA_PLAN_FN int32_t plan_len(int32_t kv_len, int32_t max_blocks, int32_t block) {
   const int64_t most = (int64_t)max_blocks * block;
   return kv_len < 0 ? 0 : (kv_len > most ? (int32_t)(most > 0x7fffffff ? 0x7fffffff : most) : kv_len);
+}
+
+// What a decode call cuts its batch into where the library chose the split factor: equal shares (each sequence's blocks
+// in `splits` parts) or the balanced ranges of `workers` workers.  Costs in blocks of one workgroup: a piece costs its
+// blocks and kPlanPieceCost more (queries, first tile, the first blocks' rescales, epilogue; 96 sequences of 32 blocks in
+// 256 ranges of 12 blocks, up to two pieces each, took 107.9 us, in 192 equal shares of 16 blocks 98.4), equal shares
+// run in `rounds` rounds of one workgroup per compute unit, and a worker of a ragged batch has two pieces as a rule:
+//   total / workers + 2 kPlanPieceCost < rounds (longest / splits + kPlanPieceCost),
+// here without its divisions.
+constexpr uint32_t kPlanPieceCost = 6;
+AMLA_PLAN_FN bool plan_prefers_ranges(uint32_t total, uint32_t longest, uint32_t splits, uint32_t workers, uint32_t rounds) {
+  const uint64_t piece = (uint64_t)kPlanPieceCost * workers * splits;
+  return (uint64_t)total * splits + 2 * piece < rounds * ((uint64_t)longest * workers + piece);
 }
 
 // One piece of a worker's walk.

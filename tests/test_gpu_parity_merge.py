@@ -29,3 +29,16 @@ def test_equal_share_merge_and_row_remainders(env, flags, heads, s_q, splits):
     out, lse = run_gpu(torch, amla, case, to_dev(torch, case), variant=1, num_splits=splits, flags=flags)
     want, want_lse = orc.decode(case.q_bits, case.kv_bits, case.block_table, case.seqlens, case.softmax_scale)
     check(out, lse, want, want_lse, f"merge heads {heads} s_q {s_q} splits {splits} flags {flags}")
+
+
+@pytest.mark.parametrize("heads,s_q,lens,variant,flags",
+                         [(128, 1, [9000] + [200, 0, 65] * 20, 1, 0), (128, 2, [6000, 300, 2000, 64, 900] * 5, 0, 32),
+                          (16, 1, [16384, 128] * 30, 2, 0), (129, 1, [5000] + [0, 300] * 25, 1, 0),
+                          (16, 1, [8192] * 95 + [8191], 1, 0)])
+def test_default_decomposition_of_ragged_batches(env, heads, s_q, lens, variant, flags):
+    """No split factor given: ranges or equal shares by the batch's lengths (the last batch: equal lengths, several rounds)."""
+    torch, orc, amla, wl = env
+    case = wl.make_case("ranges", 84, batch=len(lens), s_q=s_q, heads=heads, seqlens=lens, spare_frac=0.05)
+    out, lse = run_gpu(torch, amla, case, to_dev(torch, case), variant=variant, flags=flags)
+    want, want_lse = orc.decode(case.q_bits, case.kv_bits, case.block_table, case.seqlens, case.softmax_scale)
+    check(out, lse, want, want_lse, f"ranges heads {heads} s_q {s_q}")
