@@ -126,10 +126,9 @@ typedef struct amla_desc {
   int32_t num_splits;          /* split-KV factor: each sequence's blocks are cut into this many
                                   contiguous ranges processed by separate workgroups and merged
                                   by a combine kernel.  0 = library chooses from the shape; at
-                                  most 256.  With 0, where the choice is more than one range, the
-                                  default kernels look at the lengths on the device and cut the
-                                  batch as under AMLA_FLAG_BALANCED instead if equal shares would
-                                  wait for its longest sequences (same workspace size). */
+                                  most 256.  Either way a sequence is cut by the shape and its own
+                                  length alone: its result does not depend on the batch's other
+                                  lengths (under AMLA_FLAG_BALANCED it does, in the last bits). */
   int32_t flags;               /* AMLA_FLAG_* */
   int32_t reserved;            /* must be 0 */
   void* workspace;             /* device scratch for split-KV partials; may be NULL when the

@@ -24,7 +24,6 @@
 // brought HBM -> LDS by direct-to-LDS loads (global_load_lds_dwordx4), double buffered.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -207,28 +206,11 @@ int enqueue_decode(const void* q, const void* kv_cache, const int32_t* block_tab
   p.part_o = (ns > 1 || balanced) ? static_cast<float*>(workspace) : nullptr;
   p.part_lse = ns > 1 ? p.part_o + (size_t)ns * n_rows * kDv : nullptr;
   if (balanced) p.part_lse = p.part_o + ((size_t)ns + desc->batch - 1) * p.rows * kDv;
-  // Where the library chose the split factor the default kernels may choose ranges instead, from the lengths: one round of
-  // workers, as far as their batch - 1 slots more than workers fit in the workspace that equal shares need, half of which
-  // FP16 rows leave free.  Not where the longest share there can be is short: looking at the lengths costs each kernel
-  // 0.5 - 1 us, and the pieces' fixed cost leaves ranges little to gain.
-  const long long at_once = std::max<long long>(1, std::min(256, device_cu_count() / p.n_tiles));
-  const long long shares = (long long)ns * desc->batch;
-  const int longest_share = (desc->max_blocks_per_seq + ns - 1) / ns;
-  p.n_workers = 0;
-  p.n_rounds = (int)((shares + at_once - 1) / at_once);
-  if (desc->num_splits == 0 && ns > 1 && desc->batch > 1 && !balanced && !uses_transposed(desc) &&
-      p.n_rounds * (longest_share + kPlanPieceCost) >= 4 * kPlanPieceCost) {
-    const long long room = shares * (long long)((kDv + 1) * sizeof(float)) / (long long)(kDv * 2 + sizeof(float));
-    p.n_workers = (int)std::min(at_once, room - desc->batch + 1);
-    const size_t slots = (size_t)std::max<long long>(shares, (long long)p.n_workers + desc->batch - 1);
-    p.part_lse = reinterpret_cast<float*>(reinterpret_cast<uint16_t*>(p.part_o) + slots * p.rows * kDv);
-  }
 
   hipStream_t stream = static_cast<hipStream_t>(desc->stream);
   const long long streams_pad = ((long long)p.n_streams + 7) / 8 * 8;
   // (the equal-share row-rescale kernels deal sequences, not streams, over the 8 XCDs: the batch is padded)
-  long long grid = (!uses_transposed(desc) && !balanced ? ((long long)desc->batch + 7) / 8 * 8 * ns : streams_pad) * p.n_tiles;
-  grid = std::max(grid, ((long long)p.n_workers + 7) / 8 * 8 * p.n_tiles);
+  const long long grid = (!uses_transposed(desc) && !balanced ? ((long long)desc->batch + 7) / 8 * 8 * ns : streams_pad) * p.n_tiles;
   if (grid > 0x7fffffffll) return AMLA_ERR_UNSUPPORTED;
   const bool lazy = (desc->flags & AMLA_FLAG_LAZY_RESCALE) != 0;
   AmlaDecodeKernel kern = nullptr;
@@ -253,14 +235,13 @@ int enqueue_decode(const void* q, const void* kv_cache, const int32_t* block_tab
   if (!allow_large_lds(reinterpret_cast<const void*>(kern), lds_bytes)) return AMLA_ERR_LAUNCH;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), lds_bytes, stream, p);
   if (hipGetLastError() != hipSuccess) return AMLA_ERR_LAUNCH;
-  if (balanced || p.n_workers > 0) {
+  if (balanced) {
     // (the row-rescale kernels leave their partial rows in FP16, the transposed-accumulator kernels in FP32)
     const auto combine = uses_transposed(desc) ? amla_combine_balanced_kernel<false> : amla_combine_balanced_kernel<true>;
     const int rows_per_wave = n_rows > 4096 ? 2 : 1;
     const size_t per_wg = (size_t)kMergeRows * rows_per_wave, groups = (p.rows + per_wg - 1) / per_wg;
     hipLaunchKernelGGL(combine, dim3((unsigned)(desc->batch * groups)), dim3(64 * kMergeRows), 0, stream, p.part_o,
-                       p.part_lse, p.seqlens, p.out, p.lse, p.batch, p.rows, balanced ? ns : p.n_workers, p.max_blocks,
-                       balanced ? 0 : ns, p.n_rounds, rows_per_wave);
+                       p.part_lse, p.seqlens, p.out, p.lse, p.batch, p.rows, ns, p.max_blocks, rows_per_wave);
     if (hipGetLastError() != hipSuccess) return AMLA_ERR_LAUNCH;
   } else if (ns > 1) {
     const auto combine = uses_transposed(desc) ? amla_combine_kernel<false> : amla_combine_kernel<true>;

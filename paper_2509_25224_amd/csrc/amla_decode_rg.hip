@@ -900,9 +900,7 @@ __device__ __forceinline__ void find_block(const DecodeParams& p, const int g, c
   }
 }
 
-// Equal-share decomposition: workgroup = (sequence, split, 128-row tile).  Where the library chose the split factor
-// (p.n_workers > 0) the workgroups look at the lengths first and take the ranges of the balanced decomposition instead
-// if equal shares would wait for the longest sequence (plan_prefers_ranges; the merge decides by the same rule).
+// Equal-share decomposition: workgroup = (sequence, split, 128-row tile).
 template <int VARIANT, bool ITER512>
 __global__ __launch_bounds__(kThreads) AMLA_ONE_WAVE_PER_SIMD
 void amla_decode_rg_kernel(const DecodeParams p) {
@@ -921,72 +919,22 @@ void amla_decode_rg_kernel(const DecodeParams p) {
   const int slot = blockIdx.x >> 3;
   const int group = slot / p.n_tiles;
   const int tile = slot % p.n_tiles;
-
-  // as a worker: neighbouring workers, which often share a sequence's query rows, on one XCD
-  const int per_xcd = (p.n_workers + 7) / 8;
-  const int worker = xcd * per_xcd + group;
-  int b = (group / p.n_splits) * 8 + xcd;
-  const bool there = b < p.batch;
+  const int b = (group / p.n_splits) * 8 + xcd;
+  const int split = group % p.n_splits;
+  if (b >= p.batch) return;
 
   // The first 64 entries of the sequence's block-table row are asked for together with its length, one per lane:
   // a share that starts within them (any share of a sequence of up to 4096 keys, the first shares of a longer
-  // one) then has its first entry without a second memory round trip before the first tile can be requested.  (Also
-  // before it is known whether ranges are the better choice.)
-  int lane_entry = 0, len = 0;
-  auto ask = [&]() {
-    lane_entry = (p.table + (size_t)b * p.max_blocks)[min(lane, p.max_blocks - 1)];
-    len = p.seqlens[b];
-  };
-  if (there) ask();
-
-  int g0 = 0, g1 = 0, j = 0;   // this worker's global blocks; none (g1 = 0) with equal shares
-  if (p.n_workers > 0) {
-    const BatchBlocks blocks = batch_blocks(p.seqlens, p.batch, p.max_blocks, 0, lane);
-    if (plan_prefers_ranges(blocks.total, blocks.longest, p.n_splits, p.n_workers, p.n_rounds)) {
-      if (group >= per_xcd || worker >= p.n_workers) return;
-      g0 = plan_range_begin(worker, blocks.total, p.n_workers);
-      g1 = plan_range_begin(worker + 1, blocks.total, p.n_workers);
-      if (g0 >= g1) return;
-      find_block(p, g0, lane, b, j);
-      if (b < 0) return;   // unreachable when g0 < total
-      ask();
-    }
-  }
-  if (g1 == 0 && !there) return;
-
-  bool first_piece = true;
-  for (;;) {
-    const int kv_len = plan_len(__builtin_amdgcn_readfirstlane(len), p.max_blocks, kBlock);
-    const int nb = plan_blocks_of(kv_len, kBlock);
-    const bool ranges = g1 > 0;
-    int j0, j1;
-    bool whole;
-    size_t part_row0;
-    if (ranges) {
-      j0 = j;
-      j1 = min(nb, j + (g1 - g0));
-      whole = j0 == 0 && j1 == nb;
-      part_row0 = (size_t)(worker + b) * p.rows;
-    } else {
-      const int split = group % p.n_splits;
-      j0 = (int)plan_range_begin(split, nb, p.n_splits);
-      j1 = (int)plan_range_begin(split + 1, nb, p.n_splits);
-      whole = p.n_splits == 1;
-      part_row0 = ((size_t)split * p.batch + b) * p.rows;
-    }
-    const bool have_entry = j0 < 64;
-    const int entry = __builtin_amdgcn_readlane(lane_entry, j0 & 63);
-    if (!ranges || j0 < j1) {   // (a range passes over sequences without blocks)
-      decode_piece<VARIANT, false, ITER512>(p, smem, lane, wave, b, kv_len, j0, j1, tile, whole, part_row0, 0, 0, first_piece,
-                                            have_entry, entry);
-      first_piece = false;
-    }
-    g0 += j1 - j0;
-    j = 0;
-    ++b;
-    if (g0 >= g1 || b >= p.batch) break;
-    ask();
-  }
+  // one) then has its first entry without a second memory round trip before the first tile can be requested.
+  const int lane_entry = (p.table + (size_t)b * p.max_blocks)[min(lane, p.max_blocks - 1)];
+  const int kv_len = plan_len(__builtin_amdgcn_readfirstlane(p.seqlens[b]), p.max_blocks, kBlock);
+  const int nb = plan_blocks_of(kv_len, kBlock);
+  const int j0 = (int)plan_range_begin(split, nb, p.n_splits);
+  const int j1 = (int)plan_range_begin(split + 1, nb, p.n_splits);
+  const bool have_entry = j0 < 64;
+  const int entry = __builtin_amdgcn_readlane(lane_entry, j0 & 63);
+  decode_piece<VARIANT, false, ITER512>(p, smem, lane, wave, b, kv_len, j0, j1, tile, p.n_splits == 1,
+                                        ((size_t)split * p.batch + b) * p.rows, 0, 0, true, have_entry, entry);
 }
 
 // Balanced decomposition (ragged batches, causal mask among the s_q tokens, per-sequence query counts):

@@ -81,11 +81,6 @@ struct DecodeParams {
   int32_t causal_span;      // s_q - 1 under the causal mask among the s_q query tokens, else 0
   int32_t s_q;              // query tokens per sequence in the q array
   const int32_t* q_lens;    // [B] query tokens sequence b really has (<= s_q), or null: s_q everywhere
-  // equal-share row-rescale kernels, where the library chose the split factor: the number of workers the batch is cut
-  // into instead if its lengths make equal shares the slower choice (0: equal shares whatever the lengths), and how
-  // many rounds of workgroups equal shares take
-  int32_t n_workers;
-  int32_t n_rounds;
 };
 
 // A row's shift that puts its limit before every key: the row of a padding token.
@@ -173,36 +168,35 @@ __device__ __forceinline__ int wave_inclusive_scan(int v, int lane) {
   return v;
 }
 
-// Sums and the maximum of non-negative values over a wave, in every lane.  On the vector unit's lane shifts: six
-// dependent shuffles through LDS are about 700 cycles, and these stand before a workgroup's first load.
+// v <- the sum of v over the wave, in every lane.  On the vector unit's lane shifts: six dependent shuffles through LDS
+// are about 700 cycles, and this stands before a workgroup's first load.
 #ifndef AMLA_TARGET_HOOKS
 template <int CTRL, int ROWS>
 __device__ __forceinline__ int lane_shift(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, true); }
-#define AMLA_WAVE_REDUCE(v, op)                                                                        \
-  do {                                                                                                 \
-    v = op(v, (lane_shift<0x111, 0xf>(v))); /* row_shr 1, 2, 4, 8: lane 15 of a row has the row's */   \
-    v = op(v, (lane_shift<0x112, 0xf>(v)));                                                            \
-    v = op(v, (lane_shift<0x114, 0xf>(v)));                                                            \
-    v = op(v, (lane_shift<0x118, 0xf>(v)));                                                            \
-    v = op(v, (lane_shift<0x142, 0xa>(v))); /* row_bcast 15 into rows 1 and 3 */                       \
-    v = op(v, (lane_shift<0x143, 0xc>(v))); /* row_bcast 31 into rows 2 and 3: lane 63 has them all */ \
-    v = __builtin_amdgcn_readlane(v, 63);                                                              \
+#define AMLA_WAVE_SUM(v)                                                                         \
+  do {                                                                                           \
+    v += lane_shift<0x111, 0xf>(v); /* row_shr 1, 2, 4, 8: lane 15 of a row has the row's */     \
+    v += lane_shift<0x112, 0xf>(v);                                                              \
+    v += lane_shift<0x114, 0xf>(v);                                                              \
+    v += lane_shift<0x118, 0xf>(v);                                                              \
+    v += lane_shift<0x142, 0xa>(v); /* row_bcast 15 into rows 1 and 3 */                         \
+    v += lane_shift<0x143, 0xc>(v); /* row_bcast 31 into rows 2 and 3: lane 63 has them all */   \
+    v = __builtin_amdgcn_readlane(v, 63);                                                        \
   } while (0)
 #else
-#define AMLA_WAVE_REDUCE(v, op)                                       \
-  do {                                                                \
-    for (int o = 32; o > 0; o >>= 1) v = op(v, __shfl_xor(v, o));     \
+#define AMLA_WAVE_SUM(v)                                    \
+  do {                                                      \
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o); \
   } while (0)
 #endif
-#define AMLA_PLUS(x, y) ((x) + (y))
 
-// Blocks of all sequences, of the longest one, and this lane's part of those before sequence b (AMLA_WAVE_REDUCE has the
-// sum).  Kept to a few instructions: where a merge has a wave for every row, all of them do this.
+// Blocks of all sequences, and this lane's part of those before sequence b (AMLA_WAVE_SUM has the sum).  Kept to a few
+// instructions: where a merge has a wave for every row, all of them do this.
 struct BatchBlocks {
-  int total, longest, before;
+  int total, before;
 };
 __device__ __forceinline__ BatchBlocks batch_blocks(const int32_t* seqlens, int batch, int max_blocks, int b, int lane) {
-  BatchBlocks s = {0, 0, 0};
+  BatchBlocks s = {0, 0};
   const int most = plan_len(0x7fffffff, max_blocks, kBlock);
   constexpr int kAhead = 4;   // 256 lengths in one round trip
   for (int c = 0; c < batch; c += 64 * kAhead) {
@@ -214,12 +208,10 @@ __device__ __forceinline__ BatchBlocks batch_blocks(const int32_t* seqlens, int 
       if (c + 64 * k >= batch) break;
       const int nb = (int)(((unsigned)min(max(len[k], 0), most) + (kBlock - 1)) / kBlock);
       s.total += nb;
-      s.longest = max(s.longest, nb);
       s.before += c + 64 * k + lane < b ? nb : 0;
     }
   }
-  AMLA_WAVE_REDUCE(s.total, AMLA_PLUS);
-  AMLA_WAVE_REDUCE(s.longest, max);
+  AMLA_WAVE_SUM(s.total);
   return s;
 }
 

@@ -52,19 +52,6 @@ AMLA_PLAN_FN int32_t plan_len(int32_t kv_len, int32_t max_blocks, int32_t block)
   return kv_len < 0 ? 0 : (kv_len > most ? (int32_t)(most > 0x7fffffff ? 0x7fffffff : most) : kv_len);
 }
 
-// What a decode call cuts its batch into where the library chose the split factor: equal shares (each sequence's blocks
-// in `splits` parts) or the balanced ranges of `workers` workers.  Costs in blocks of one workgroup: a piece costs its
-// blocks and kPlanPieceCost more (queries, first tile, the first blocks' rescales, epilogue; 96 sequences of 32 blocks in
-// 256 ranges of 12 blocks, up to two pieces each, took 107.9 us, in 192 equal shares of 16 blocks 98.4), equal shares
-// run in `rounds` rounds of one workgroup per compute unit, and a worker of a ragged batch has two pieces as a rule:
-//   total / workers + 2 kPlanPieceCost < rounds (longest / splits + kPlanPieceCost),
-// here without its divisions.
-constexpr uint32_t kPlanPieceCost = 6;
-AMLA_PLAN_FN bool plan_prefers_ranges(uint32_t total, uint32_t longest, uint32_t splits, uint32_t workers, uint32_t rounds) {
-  const uint64_t piece = (uint64_t)kPlanPieceCost * workers * splits;
-  return (uint64_t)total * splits + 2 * piece < rounds * ((uint64_t)longest * workers + piece);
-}
-
 // One piece of a worker's walk.
 struct PlanPiece {
   int32_t b;       // sequence

@@ -1,0 +1,45 @@
+"""The default entry (no split factor given): a call is cut by its shape alone, so that a sequence's bits are those of the
+call with the same factor given explicitly and do not move with its neighbours' lengths.  The library's source compiled
+for the host (see test_cpu_build.py), under AddressSanitizer with a workspace of exactly the documented size."""
+import numpy as np
+import pytest
+
+from paper_2509_25224_amd import workloads as wl
+from test_cpu_build import check, exe, run_cpu  # noqa: F401
+
+LONG_AND_EMPTY = [0] * 20 + [5000] + [40, 0] * 9 + [64, 65, 129] + [0] * 18   # one long sequence between short and empty ones
+
+
+def _case(heads, s_q, lens, columns=0):
+    """`columns`: a block table laid out for longer sequences (the library splits by it)."""
+    case = wl.make_case("default", 83, batch=len(lens), s_q=s_q, heads=heads, seqlens=lens, spare_frac=0.1)
+    if columns > case.max_blocks_per_seq:
+        wide = np.full((case.batch, columns), -1, np.int32)
+        wide[:, :case.max_blocks_per_seq] = case.block_table
+        case.block_table = wide
+    return case
+
+
+@pytest.mark.parametrize("heads,s_q,lens,columns,variant,flags,static",
+                         [(16, 1, LONG_AND_EMPTY, 0, 1, 0, False), (3, 1, LONG_AND_EMPTY, 0, 0, 32, True),
+                          (129, 1, [5000] + [0, 63] * 15, 0, 2, 0, False), (16, 1, [700, 500], 600, 1, 0, False),
+                          (16, 1, [600, 0, 520], 0, 1, 0, False), (130, 1, [700, 0, 65], 200, 0, 0, True)])
+def test_default_is_the_explicit_split(exe, tmp_path, heads, s_q, lens, columns, variant, flags, static):
+    case = _case(heads, s_q, lens, columns)
+    out, lse, splits = run_cpu(exe, tmp_path, case, variant, flags=flags, static_ws=static)
+    assert splits > 1
+    want, want_lse, _ = run_cpu(exe, tmp_path, case, variant, flags=flags, ns=splits)
+    assert np.array_equal(out, want) and np.array_equal(lse, want_lse)
+    check(out, lse, case)
+
+
+def test_a_sequence_does_not_depend_on_its_neighbours_lengths(exe, tmp_path):
+    case = _case(16, 1, [900, 5000] + [40, 0] * 29)
+    out, lse, splits = run_cpu(exe, tmp_path, case, 1)
+    assert splits > 1
+    case.seqlens = case.seqlens.copy()
+    case.seqlens[1] = 1000
+    alone, alone_lse, same_splits = run_cpu(exe, tmp_path, case, 1)
+    assert same_splits == splits
+    keep = np.arange(case.batch) != 1
+    assert np.array_equal(out[keep], alone[keep]) and np.array_equal(lse[keep], alone_lse[keep])

@@ -36,9 +36,14 @@ def test_equal_share_merge_and_row_remainders(env, flags, heads, s_q, splits):
                           (16, 1, [16384, 128] * 30, 2, 0), (129, 1, [5000] + [0, 300] * 25, 1, 0),
                           (16, 1, [8192] * 95 + [8191], 1, 0)])
 def test_default_decomposition_of_ragged_batches(env, heads, s_q, lens, variant, flags):
-    """No split factor given: ranges or equal shares by the batch's lengths (the last batch: equal lengths, several rounds)."""
+    """No split factor given: bit for bit the call with the library's factor given (the last batch: several rounds)."""
     torch, orc, amla, wl = env
     case = wl.make_case("ranges", 84, batch=len(lens), s_q=s_q, heads=heads, seqlens=lens, spare_frac=0.05)
     out, lse = run_gpu(torch, amla, case, to_dev(torch, case), variant=variant, flags=flags)
     want, want_lse = orc.decode(case.q_bits, case.kv_bits, case.block_table, case.seqlens, case.softmax_scale)
     check(out, lse, want, want_lse, f"ranges heads {heads} s_q {s_q}")
+    splits = amla.amla_effective_splits(amla.make_desc(case.batch, s_q, heads, case.num_blocks, case.max_blocks_per_seq,
+                                                       variant, 0, flags))
+    assert splits > 1
+    same, same_lse = run_gpu(torch, amla, case, to_dev(torch, case), variant=variant, num_splits=splits, flags=flags)
+    assert np.array_equal(out, same) and np.array_equal(lse, same_lse)
