@@ -52,6 +52,10 @@ AMLA_PLAN_FN int32_t plan_len(int32_t kv_len, int32_t max_blocks, int32_t block)
   return kv_len < 0 ? 0 : (kv_len > most ? (int32_t)(most > 0x7fffffff ? 0x7fffffff : most) : kv_len);
 }
 
+// first worker on XCD x (x may be 8: one past the last XCD's workers): neighbours side by side, and as many on every XCD
+// as any dealing could give it, ceil(W / 8) at most
+AMLA_PLAN_FN int32_t plan_xcd_begin(int32_t x, int32_t W) { return x * W / 8; }
+
 // One piece of a worker's walk.
 struct PlanPiece {
   int32_t b;       // sequence

@@ -1,5 +1,9 @@
 """The balanced decomposition's integer arithmetic (csrc/amla_plan.h), run on the host through the
 C ABI: the same routines the decode and combine kernels use to decide who owns which block."""
+import ctypes
+import os
+import subprocess
+
 import numpy as np
 import pytest
 
@@ -92,3 +96,24 @@ def test_plan_rejects_bad_arguments():
         amla.amla_plan_segments([10, -1], 4)
     with pytest.raises(amla.AmlaError):
         amla.amla_plan_segments([10], 0)
+
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2509_25224_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    """The routines of amla_plan.h themselves, as the host compiler builds them."""
+    tmp = tmp_path_factory.mktemp("plan")
+    src = tmp / "plan.cpp"
+    src.write_text('#include "amla_plan.h"\nextern "C" int xcd_begin(int x, int w) { return plan_xcd_begin(x, w); }\n')
+    subprocess.run(["g++", "-O2", "-shared", "-fPIC", "-I" + CSRC, "-o", str(tmp / "plan.so"), str(src)], check=True)
+    return ctypes.CDLL(str(tmp / "plan.so"))
+
+
+def test_workers_are_dealt_evenly_over_the_xcds(plan):
+    for workers in range(1, 257):
+        first = [plan.xcd_begin(x, workers) for x in range(9)]
+        assert first[0] == 0 and first[8] == workers
+        share = np.diff(first)
+        assert share.min() == workers // 8 and share.max() == (workers + 7) // 8   # the grid has room for the latter
