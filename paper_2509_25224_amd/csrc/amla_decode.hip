@@ -246,7 +246,8 @@ int enqueue_decode(const void* q, const void* kv_cache, const int32_t* block_tab
   } else if (ns > 1) {
     const auto combine = uses_transposed(desc) ? amla_combine_kernel<false> : amla_combine_kernel<true>;
     hipLaunchKernelGGL(combine, dim3((unsigned)((n_rows + kMergeRows - 1) / kMergeRows)), dim3(64 * kMergeRows), 0, stream,
-                       p.part_o, p.part_lse, p.out, p.lse, (int)n_rows, ns);
+                       p.part_o, p.part_lse, n_rows * ns >= 8192 ? p.seqlens : nullptr, p.out, p.lse, (int)n_rows,
+                       p.rows, ns);
     if (hipGetLastError() != hipSuccess) return AMLA_ERR_LAUNCH;
   }
   return AMLA_OK;

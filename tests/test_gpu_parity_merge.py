@@ -34,9 +34,10 @@ def test_equal_share_merge_and_row_remainders(env, flags, heads, s_q, splits):
 @pytest.mark.parametrize("heads,s_q,lens,variant,flags",
                          [(128, 1, [9000] + [200, 0, 65] * 20, 1, 0), (128, 2, [6000, 300, 2000, 64, 900] * 5, 0, 32),
                           (16, 1, [16384, 128] * 30, 2, 0), (129, 1, [5000] + [0, 300] * 25, 1, 0),
-                          (16, 1, [8192] * 95 + [8191], 1, 0)])
+                          (16, 1, [8192] * 95 + [8191], 1, 0), (128, 1, [3000, 0, 4096] * 3 + [0] * 55, 1, 0),
+                          (128, 1, [1500, 0, 2048] * 3 + [0] * 55, 1, TRANSPOSED)])
 def test_default_decomposition_of_ragged_batches(env, heads, s_q, lens, variant, flags):
-    """No split factor given: bit for bit the call with the library's factor given (the last batch: several rounds)."""
+    """No split factor given: bit for bit the call with the library's factor given (one batch: several rounds; the last two: mostly empty slots)."""
     torch, orc, amla, wl = env
     case = wl.make_case("ranges", 84, batch=len(lens), s_q=s_q, heads=heads, seqlens=lens, spare_frac=0.05)
     out, lse = run_gpu(torch, amla, case, to_dev(torch, case), variant=variant, flags=flags)
