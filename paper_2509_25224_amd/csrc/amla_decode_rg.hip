@@ -173,9 +173,9 @@ __device__ __forceinline__ float max_over_halves(const float x) {
 //     MFMA reads what it wrote;
 //   * the epilogue waits for the last MFMA to drain before it copies the accumulator out.
 #ifndef AMLA_TARGET_HOOKS
-// Every statement that writes the accumulator names all 256 AccVGPRs as clobbered: no value of the compiler's
-// can then live in an AccVGPR across it (the register allocator would otherwise park loop-invariant values
-// there, to be overwritten by the MFMAs it cannot see).
+// Every statement that names the accumulator, to read it or to write it, names all 256 AccVGPRs as clobbered: no value of
+// the compiler's can then live in an AccVGPR across it (the register allocator would otherwise park values there, to be
+// overwritten by the MFMAs it cannot see or to overwrite what the epilogue has yet to read).
 #define AMLA_ACC_A10(n) "a" #n "0", "a" #n "1", "a" #n "2", "a" #n "3", "a" #n "4", "a" #n "5", "a" #n "6", "a" #n "7", "a" #n "8", "a" #n "9"
 #define AMLA_ACC_ALL                                                                                                  \
   "a0", "a1", "a2", "a3", "a4", "a5", "a6", "a7", "a8", "a9", AMLA_ACC_A10(1), AMLA_ACC_A10(2), AMLA_ACC_A10(3),      \
@@ -196,12 +196,6 @@ __device__ __forceinline__ void acc_clear_tile() {
   const bf16x8 z = __builtin_bit_cast(bf16x8, i32x4{0, 0, 0, 0});
   // (two idle states first: the zero operand may have been written by the VALU instruction just before)
   asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 a[%1*16:%1*16+15], %0, %0, 0" : : "v"(z), "n"(DT) : AMLA_ACC_ALL);
-}
-template <int R>
-__device__ __forceinline__ float acc_read() {
-  float x;
-  asm volatile("v_accvgpr_read_b32 %0, a[%1]" : "=v"(x) : "n"(R));
-  return x;
 }
 // The rescale of register I of all 16 tiles (the two query rows that own it), one statement: FP32 multiply, or
 // Lemma 3.1 with a guard.  Two forms of the guard:
@@ -267,9 +261,9 @@ __device__ __forceinline__ void acc_stage_rows(LDS_PTR(uint8_t) at) {
     constexpr int e = ec.value;
     const unsigned lo = (unsigned)(__UINTPTR_TYPE__)at + e * STRIDE, hi = lo + 1024;
     asm volatile(AMLA_ACC_STAGE_PAIR(0) AMLA_ACC_STAGE_PAIR(2) AMLA_ACC_STAGE_PAIR(4) AMLA_ACC_STAGE_PAIR(6)
-                 : : "v"(lo), "n"(4 * G + e) : "memory");
+                 : : "v"(lo), "n"(4 * G + e) : "memory", AMLA_ACC_ALL);
     asm volatile(AMLA_ACC_STAGE_PAIR(8) AMLA_ACC_STAGE_PAIR(10) AMLA_ACC_STAGE_PAIR(12) AMLA_ACC_STAGE_PAIR(14)
-                 : : "v"(hi), "n"(4 * G + e) : "memory");
+                 : : "v"(hi), "n"(4 * G + e) : "memory", AMLA_ACC_ALL);
   });
 }
 __device__ __forceinline__ void acc_idle(void) { asm volatile("s_nop 7"); }

@@ -148,6 +148,17 @@ def test_row_rescale_kernels_keep_the_compiler_out_of_the_accumulator(row_asm_pa
             assert not [ln for ln in _steady_loop(body) if ln.startswith("scratch_")], name
 
 
+def test_every_statement_that_names_the_accumulator_claims_it():
+    """The accumulator's AccVGPRs are addressed by name: a statement that does so without naming them all as clobbered
+    would leave the compiler free to keep a value of its own in one up to there."""
+    text = open(SRC_ROW).read()
+    statements = [m.group(0) for m in re.finditer(r"asm volatile\((?:[^;]|;(?=\s*\\))*\);", text)]
+    naming = [s for s in statements if "a[%" in s or "AMLA_ACC_EACH_FOUR" in s or "AMLA_ACC_STAGE" in s]
+    assert len(naming) >= 6
+    for s in naming:
+        assert "AMLA_ACC_ALL" in s, s
+
+
 if __name__ == "__main__" and "--write" in sys.argv:
     import tempfile
     h = kernel_hashes(device_assembly(tempfile.mkdtemp()))
