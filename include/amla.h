@@ -248,7 +248,8 @@ int amla_device_info(int32_t* compute_units, int32_t* clock_khz);
 
 /*
  * amla_plan_segments -- host-only view of the balanced decomposition (AMLA_FLAG_BALANCED), computed
- * with the same integer routines the kernels use; for tests and for sizing.  `seqlens` is a HOST
+ * for up to 256 workers (as many as amla_decode has) with the routines the kernels use, above that in
+ * 64-bit integers; for tests and for sizing.  `seqlens` is a HOST
  * array of `batch` lengths.  Writes up to `capacity` pieces as rows of six int32
  * (worker, sequence, first block, end block, workspace slot, covers-whole-sequence) to `pieces`
  * (host) in the order the workers produce them, the number of pieces to *n_pieces, and for every

@@ -3,7 +3,7 @@
 // ranges of equal length.  A worker walks its range sequence by sequence; every (worker, sequence)
 // pair it touches is a *piece* with its own softmax state, and pieces of one sequence are merged
 // afterwards exactly like split-KV partials (the merge rule of Algorithm 1's update).  This file
-// holds the integer arithmetic shared by the decode kernel, the combine kernel and the host-side
+// holds the arithmetic shared by the decode kernel, the combine kernel and the host-side
 // test entry point, so that all three agree on who owns which block and which slot.
 //
 // Facts used by the callers (checked by the CPU tests through amla_plan_segments):

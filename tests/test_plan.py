@@ -1,5 +1,6 @@
 """The balanced decomposition's integer arithmetic (csrc/amla_plan.h), run on the host through the
-C ABI: the same routines the decode and combine kernels use to decide who owns which block."""
+C ABI (up to 256 workers, as many as a call can have, with the routines by which the kernels decide who owns which block;
+above that in exact integers)."""
 import ctypes
 import os
 import subprocess
@@ -106,7 +107,24 @@ def plan(tmp_path_factory):
     """The routines of amla_plan.h themselves, as the host compiler builds them."""
     tmp = tmp_path_factory.mktemp("plan")
     src = tmp / "plan.cpp"
-    src.write_text('#include "amla_plan.h"\nextern "C" int xcd_begin(int x, int w) { return plan_xcd_begin(x, w); }\n')
+    src.write_text(r'''
+#include "amla_plan.h"
+extern "C" int xcd_begin(int x, int w) { return plan_xcd_begin(x, w); }
+// disagreements of the float and double forms with the integer ones, T blocks, 1 .. 256 workers: the first block of every
+// worker, and the owner of the blocks around it
+extern "C" long plan_mismatches(int64_t T) {
+  long bad = 0;
+  for (int64_t W = 1; W <= 256; ++W)
+    for (int64_t w = 0; w <= W; ++w) {
+      const int64_t first = plan_worker_begin(w, T, W);
+      bad += (int64_t)plan_range_begin((uint32_t)w, (uint32_t)T, (uint32_t)W) != first;
+      for (int64_t g = first - 1; g <= first + 1; ++g)
+        if (g >= 0 && g < T)
+          bad += (int64_t)plan_range_of_block((uint32_t)g, (uint32_t)T, (uint32_t)W) != plan_worker_of_block(g, T, W);
+    }
+  return bad;
+}
+''')
     subprocess.run(["g++", "-O2", "-shared", "-fPIC", "-I" + CSRC, "-o", str(tmp / "plan.so"), str(src)], check=True)
     return ctypes.CDLL(str(tmp / "plan.so"))
 
@@ -117,3 +135,12 @@ def test_workers_are_dealt_evenly_over_the_xcds(plan):
         assert first[0] == 0 and first[8] == workers
         share = np.diff(first)
         assert share.min() == workers // 8 and share.max() == (workers + 7) // 8   # the grid has room for the latter
+
+
+def test_the_kernels_arithmetic_is_exact(plan):
+    """W <= 256 workers, T < 2^31 blocks: small totals, totals around multiples of the worker counts, the largest ones."""
+    plan.plan_mismatches.restype, plan.plan_mismatches.argtypes = ctypes.c_long, [ctypes.c_int64]
+    totals = set(range(1, 700)) | {2 ** k + d for k in range(10, 32) for d in (-2, -1, 0, 1)}
+    totals |= {w * m + d for w in (3, 85, 127, 255, 256) for m in (77, 4099, (2 ** 31 - 2) // w) for d in (-1, 0, 1)}
+    for total in sorted(t for t in totals if t < 2 ** 31):
+        assert plan.plan_mismatches(total) == 0, total
