@@ -153,8 +153,9 @@ int choose_splits(const amla_desc* d) {
   }
   // Equal shares: the split factor that a small cost model likes best, in units of one 64-key block of one
   // workgroup.  A workgroup costs its share of the longest possible sequence plus a fixed part (prologue,
-  // epilogue; more when it writes FP32 partial rows); the workgroups run in rounds of one per compute unit; the
-  // combine kernel costs a little per split.  At least four blocks per share, at most 64 shares.  (Measured at
+  // epilogue; more when it writes partial rows); the workgroups run in rounds of one per compute unit; the
+  // combine kernel costs a little per split.  (The costs were fitted to FP32 partial rows and a slower merge; the factors
+  // they lead to are what the tests pin.)  At least four blocks per share, at most 64 shares.  (Measured at
   // batch 96, two tokens, 4096 keys: 281 us unsplit, 320 us in two shares, 343 us in four -- 192 workgroups
   // on 256 compute units are better left alone than cut into one and a half rounds.)
   const long long base = (long long)d->batch * tiles;       // workgroups without splitting
@@ -238,6 +239,9 @@ int enqueue_decode(const void* q, const void* kv_cache, const int32_t* block_tab
   if (balanced) {
     // (the row-rescale kernels leave their partial rows in FP16, the transposed-accumulator kernels in FP32)
     const auto combine = uses_transposed(desc) ? amla_combine_balanced_kernel<false> : amla_combine_balanced_kernel<true>;
+    // Two rows a wave halve the waves that work out the plan, which is worth it once the merge fills the chip several
+    // times over: one against two, us a call, 2048 rows 56.3 / 59.2, 4096 rows 74.4 / 74.5, 8192 rows of 16 a sequence
+    // 153.7 / 151.3, 32768 rows 95.2 / 92.5.
     const int rows_per_wave = n_rows > 4096 ? 2 : 1;
     const size_t per_wg = (size_t)kMergeRows * rows_per_wave, groups = (p.rows + per_wg - 1) / per_wg;
     hipLaunchKernelGGL(combine, dim3((unsigned)(desc->batch * groups)), dim3(64 * kMergeRows), 0, stream, p.part_o,

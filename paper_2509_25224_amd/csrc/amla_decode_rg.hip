@@ -284,10 +284,12 @@ __device__ __forceinline__ void acc_stage_rows(LDS_PTR(uint8_t) at) {
 #endif
 
 // One piece of the decode loop: blocks [j0, j1) of sequence b for the 128 rows of row tile `tile`, one
-// softmax state per row, result written in final form (to_final) or as an FP32 partial row set starting at
-// row part_row0 of the workspace.  causal_shift (per lane: keys between this lane's row limit and the
-// sequence's end; kNoKeys for the row of a padding token) and mask_span (wave-uniform: the piece's largest
-// shift) are 0 without a mask.
+// softmax state per row, result written in final form (to_final) or as a set of partial rows (FP16, with an FP32
+// log-sum-exp each) starting at row part_row0 of the workspace.  causal_shift (per lane: keys between this lane's
+// row limit and the sequence's end; kNoKeys for the row of a padding token) and mask_span (wave-uniform: the
+// piece's largest shift) are 0 without a mask.  first_piece: the workgroup has not worked a piece before this one,
+// so that nobody can still be reading LDS.  have_entry: the caller already holds the block-table entry of block j0
+// (entry; not used otherwise).
 template <int VARIANT, bool MASKED, bool ITER512>
 __device__ __forceinline__ void decode_piece(const DecodeParams& p, LDS_PTR(uint8_t) smem, const int lane,
                                              const int wave, const int b, const int kv_len, const int j0,

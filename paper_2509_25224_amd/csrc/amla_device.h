@@ -109,7 +109,6 @@ __device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
 
 // two FP32 values as a pair of FP16 (round to nearest even), lo in the low half
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ unsigned pack_f16(float lo, float hi) {
   f32x2 v = {lo, hi};
