@@ -43,3 +43,14 @@ def test_a_sequence_does_not_depend_on_its_neighbours_lengths(exe, tmp_path):
     assert same_splits == splits
     keep = np.arange(case.batch) != 1
     assert np.array_equal(out[keep], alone[keep]) and np.array_equal(lse[keep], alone_lse[keep])
+
+
+def test_more_pieces_than_a_wave_merge_to_the_same_bits(exe, tmp_path):
+    """50 blocks in 50 shares of one, and in 100 shares of which 50 are empty: the same pieces, so the same merge, also
+    where it takes more than one pass over the pieces."""
+    case = _case(24, 1, [50 * 64 - 7, 50 * 64])
+    for flags in (0, 128):   # FP16 and FP32 partial rows
+        out, lse, _ = run_cpu(exe, tmp_path, case, 1, flags=flags, ns=100)
+        want, want_lse, _ = run_cpu(exe, tmp_path, case, 1, flags=flags, ns=50)
+        assert np.array_equal(out, want) and np.array_equal(lse, want_lse)
+        check(out, lse, case)
