@@ -376,24 +376,25 @@ __device__ __forceinline__ void decode_piece(const DecodeParams& p, LDS_PTR(uint
   // touch 32 rows for 32 bytes each (36 of them took 5.3 us from the kernel's entry on, whatever the load on the memory
   // system), so the rows come through LDS in whole lines, in two halves of 36 chunks: each wave through its own quarter of
   // the second tile buffer, which the second tile enters only behind the first block's barrier; the first tile is on
-  // its way meanwhile.  (One sequence of 3001 keys 29.8 -> 28.0 us a call, 12 of up to 2100 37.8 -> 36.3.)  Chunks past
-  // the end of the sequence's row range repeat the last one (valid memory); the results of such rows are never stored.
+  // its way meanwhile.  (One sequence of 3001 keys 29.8 -> 28.0 us a call, 12 of up to 2100 37.8 -> 36.3.)  Rows past the
+  // end of the sequence's row range are its row 0 (valid memory): their results are never stored, but all 32 rows of a
+  // wave take part in the decision to keep the reference.
   const int row_w = tile * kRowsPerWg + wave * 32;   // the wave's first row
   LDS_PTR(uint8_t) q_stage = smem + kRgTileBytes + wave * (kRgTileBytes / 4);
-  const uint8_t* q_base = reinterpret_cast<const uint8_t*>(p.q) + ((size_t)b * p.rows + row_w) * kRowBytes;
-  unsigned q_off[kQStageLoads];   // chunk 64 n + lane of the staged half: row (64 n + lane) / 37
+  const uint8_t* q_base = reinterpret_cast<const uint8_t*>(p.q) + (size_t)b * p.rows * kRowBytes;
+  unsigned q_off[kQStageLoads];   // chunk 64 n + lane of the staged half: row (64 n + lane) / 37 (at most 2^20 rows: 32 bits)
   {
-    const unsigned most = (unsigned)((min(32, p.rows - row_w) - 1) * kRowBytes + 36 * 16);
+    const unsigned end = (unsigned)p.rows * kRowBytes;
     int ql = lane;
     AMLA_OPAQUE(ql);   // (hoisted out of the loop over pieces, the 19 offsets would be spilled)
-    unsigned cc = ql < 37 ? ql : ql - 37;
-    unsigned off = (ql < 37 ? 0 : kRowBytes) + 16 * cc;
+    unsigned cc = 16 * (ql < 37 ? ql : ql - 37);   // the chunk's place in its row
+    unsigned off = (unsigned)(row_w + (ql < 37 ? 0 : 1)) * kRowBytes + cc;
 #pragma unroll
     for (int n = 0; n < kQStageLoads; ++n) {
-      q_off[n] = min(off, most);
-      const bool wrap = cc >= 37 - 27;   // 64 chunks on: one row and 27 chunks
-      off += kRowBytes + 27 * 16 + (wrap ? kRowBytes - 37 * 16 : 0);
-      cc = wrap ? cc - 10 : cc + 27;
+      q_off[n] = off < end ? off : cc;
+      const bool wrap = cc >= 16 * (37 - 27);   // 64 chunks on: one row and 27 chunks
+      off += kRowBytes + 16 * 27 + (wrap ? kRowBytes - 16 * 37 : 0);
+      cc = wrap ? cc - 16 * 10 : cc + 16 * 27;
     }
   }
   // The odd chunk of a staged row is the one behind it for the first half, the one before it for the second.

@@ -54,3 +54,20 @@ def test_more_pieces_than_a_wave_merge_to_the_same_bits(exe, tmp_path):
         want, want_lse, _ = run_cpu(exe, tmp_path, case, 1, flags=flags, ns=50)
         assert np.array_equal(out, want) and np.array_equal(lse, want_lse)
         check(out, lse, case)
+
+
+@pytest.mark.parametrize("variant", [0, 1, 2])
+def test_rows_past_the_end_count_as_the_sequences_first(exe, tmp_path, variant):
+    """A wave's 32 rows share the decision to keep the reference: 24 rows give the bits of 32 rows whose last eight repeat
+    row 0.  (The last row is zero but for eight large values in its second half: rows made of those would decide otherwise.)"""
+    lens = [700, 640, 500, 65, 900, 1000]
+    short = wl.make_case("rows", 85, batch=6, s_q=1, heads=24, seqlens=lens)
+    full = wl.make_case("rows", 85, batch=6, s_q=1, heads=32, seqlens=lens)
+    full.kv_bits, full.block_table = short.kv_bits, short.block_table
+    last = np.zeros(576, np.float32)
+    last[288:296] = 32
+    short.q_bits[:, :, 23] = wl.f32_to_bf16_bits(last)
+    full.q_bits = np.concatenate([short.q_bits, np.repeat(short.q_bits[:, :, :1], 8, axis=2)], axis=2)
+    out, lse, _ = run_cpu(exe, tmp_path, short, variant, ns=1)
+    want, want_lse, _ = run_cpu(exe, tmp_path, full, variant, ns=1)
+    assert np.array_equal(out, want[:, :, :24]) and np.array_equal(lse, want_lse[:, :, :24])
