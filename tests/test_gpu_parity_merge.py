@@ -48,3 +48,14 @@ def test_default_decomposition_of_ragged_batches(env, heads, s_q, lens, variant,
     assert splits > 1
     same, same_lse = run_gpu(torch, amla, case, to_dev(torch, case), variant=variant, num_splits=splits, flags=flags)
     assert np.array_equal(out, same) and np.array_equal(lse, same_lse)
+
+
+@pytest.mark.parametrize("heads,lens,splits,flags", [(128, [64, 0] + [64] * 6 + [30 * 64], 65, 0), (1100, [128, 300], 129, 0),
+                                                     (128, [64, 300], 65, TRANSPOSED), (43, [192], 193, TRANSPOSED)])
+def test_first_64_shares_without_blocks(env, heads, lens, splits, flags):
+    """Sequences of one, two and three blocks in so many shares that the first 64, what a wave merges at a time, hold nothing."""
+    torch, orc, amla, wl = env
+    case = wl.make_case("late_shares", 95, batch=len(lens), s_q=1, heads=heads, seqlens=lens, spare_frac=0.1)
+    out, lse = run_gpu(torch, amla, case, to_dev(torch, case), variant=1, num_splits=splits, flags=flags)
+    want, want_lse = orc.decode(case.q_bits, case.kv_bits, case.block_table, case.seqlens, case.softmax_scale)
+    check(out, lse, want, want_lse, f"late shares heads {heads} splits {splits} flags {flags}")

@@ -27,9 +27,26 @@ def test_chosen_factor_is_bounded(rows):
 
 @pytest.mark.parametrize("heads,variant,flags,ns", [(40, ADD, 0, 9), (8, MUL, 0, 70), (130, COMP, 0, 5), (40, ADD, TRANSPOSED, 9)])
 def test_shares_without_blocks(exe, tmp_path, heads, variant, flags, ns):
-    """More shares than a sequence has blocks, among them 70 (two passes of the merge) and sequences with none: the workspace
+    """More shares than a sequence has blocks, among them 70 (a workgroup merges a row then) and sequences with none: the workspace
     comes filled with NaN, so a partial row that nobody wrote must not count."""
     case = wl.make_case("shares", 89, batch=4, s_q=1, heads=heads, seqlens=[200, 0, 64, 330], spare_frac=0.2)
     out, lse, _ = run_cpu(exe, tmp_path, case, variant, flags=flags, ns=ns)
     check(out, lse, case)
     assert np.all(out[1] == 0) and np.all(np.isneginf(lse[1]))
+
+
+# (nb blocks in W shares: share w holds none while floor((w + 1) nb / W) = floor(w nb / W), so the first ones are the empty ones)
+@pytest.mark.parametrize("heads,lens,variant,flags,ns", [
+    (32, [64], ADD, TRANSPOSED, 256), (32, [100], MUL, TRANSPOSED, 256), (128, [64, 300], ADD, TRANSPOSED, 65),
+    (128, [64, 0] + [64] * 6 + [30 * 64], ADD, 0, 65),
+    (64, [128], COMP, TRANSPOSED, 129), (1100, [128, 300], MUL, 0, 129), (43, [192], ADD, TRANSPOSED, 193), (3200, [192], ADD, 0, 193),
+    (8, [128, 64, 0], ADD, TRANSPOSED, 129)])
+def test_first_64_shares_without_blocks(exe, tmp_path, heads, lens, variant, flags, ns):
+    """A wave merges 64 shares at a time: sequences whose first 64 hold nothing, one block each, two and three, in calls that do
+    not take the workgroup-per-row merge; all but the last have so many partial rows that the lengths are looked at first."""
+    case = wl.make_case("late_shares", 94, batch=len(lens), s_q=1, heads=heads, seqlens=lens, spare_frac=0.2)
+    n_rows = len(lens) * heads
+    assert flags == TRANSPOSED or n_rows > 16 * ns
+    assert (n_rows * ns >= 8192) == (heads != 8)
+    out, lse, _ = run_cpu(exe, tmp_path, case, variant, flags=flags, ns=ns)
+    check(out, lse, case)
