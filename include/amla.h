@@ -208,7 +208,12 @@ size_t amla_static_workspace_limit(void);
  * read.  Returns 0 for a NULL or unsupported desc.  The figure is 512 FP32 values and a log-sum-exp
  * per partial row whichever kernels run; the default kernels store their partial rows as FP16 (the
  * rows are normalised, so of the value rows' magnitude, and the merge weights them in FP32) and
- * leave the rest of the range untouched.
+ * leave the rest of the range untouched.  With the default kernels a sequence in several shares or
+ * pieces therefore needs averages of value rows within FP16's range: beyond 65504 they become
+ * infinite, below 2^-14 they keep an absolute precision of 2^-25.  A call with a factor of 1
+ * (amla_effective_splits) has BF16's range, and so have the transposed kernels, whose partial rows are
+ * FP32; num_splits = 0 is a factor of 1 where a sequence can have at most nine blocks, except under
+ * AMLA_FLAG_BALANCED.
  */
 size_t amla_workspace_bytes(const amla_desc* desc);
 

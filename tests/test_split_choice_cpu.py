@@ -50,3 +50,28 @@ def test_first_64_shares_without_blocks(exe, tmp_path, heads, lens, variant, fla
     assert (n_rows * ns >= 8192) == (heads != 8)
     out, lse, _ = run_cpu(exe, tmp_path, case, variant, flags=flags, ns=ns)
     check(out, lse, case)
+
+
+@pytest.mark.parametrize("rows", [1, 16, 32, 33, 40, 128, 256, 512])
+def test_short_tables_are_not_cut(rows):
+    """What the coarse factor (the transposed family's) leaves whole stays whole: no workspace, and results of any BF16 magnitude,
+    where partial rows are FP16."""
+    s_q, heads = (rows // 128, 128) if rows % 128 == 0 else (1, rows)
+    for batch in (1, 2, 5, 6, 14, 64, 128, 129, 255, 300):
+        for blocks in range(1, 70):
+            d = amla.make_desc(batch, s_q, heads, 20000, blocks)
+            if amla.amla_effective_splits(amla.make_desc(batch, s_q, heads, 20000, blocks, flags=amla.AMLA_FLAG_TRANSPOSED_ACC)) == 1:
+                assert amla.amla_effective_splits(d) == 1 and amla.amla_workspace_bytes(d) == 0, (batch, blocks)
+
+
+@pytest.mark.parametrize("heads,keys", [(16, 512), (40, 512), (32, 570), (128, 513)])
+def test_values_beyond_fp16(exe, tmp_path, heads, keys):
+    """Value columns of 1e5 and 1e-6 (no query looks at them) in tables of eight and nine blocks, no split factor given: every weight
+    takes part in the sum that it is divided by, so the result is the column's value to FP32 rounding, half a BF16 step at most."""
+    case = wl.make_case("range", 96, batch=1, s_q=1, heads=heads, seqlens=[keys])
+    case.q_bits[..., :2] = 0
+    bits = wl.f32_to_bf16_bits(np.array([1e5, 1e-6], np.float32))
+    case.kv_bits[..., :2] = bits
+    for variant in (MUL, ADD, COMP):
+        out, _, splits = run_cpu(exe, tmp_path, case, variant)
+        assert splits == 1 and np.all(np.abs(out[..., :2] / wl.bf16_bits_to_f32(bits) - 1) <= 2.0 ** -8), (variant, out[0, 0, 0, :2])
