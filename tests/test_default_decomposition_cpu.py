@@ -47,13 +47,22 @@ def test_a_sequence_does_not_depend_on_its_neighbours_lengths(exe, tmp_path):
 
 def test_more_pieces_than_a_wave_merge_to_the_same_bits(exe, tmp_path):
     """50 blocks in 50 shares of one, and in 100 shares of which 50 are empty: the same pieces, so the same merge, also
-    where it takes more than one pass over the pieces."""
+    where it takes more than one pass over the pieces (FP32 rows; the FP16 rows of so few go to the workgroup-per-row merge)."""
     case = _case(24, 1, [50 * 64 - 7, 50 * 64])
     for flags in (0, 128):   # FP16 and FP32 partial rows
         out, lse, _ = run_cpu(exe, tmp_path, case, 1, flags=flags, ns=100)
         want, want_lse, _ = run_cpu(exe, tmp_path, case, 1, flags=flags, ns=50)
         assert np.array_equal(out, want) and np.array_equal(lse, want_lse)
         check(out, lse, case)
+
+
+@pytest.mark.parametrize("heads,lens,flags,ns", [(1100, [4200], 0, 66), (35, [70 * 64 - 1] + [0] * 9, 8, 200)])
+def test_wave_merge_of_fp16_rows_in_several_passes(exe, tmp_path, heads, lens, flags, ns):
+    """So many rows that a wave merges each of them, 64 pieces at a time: 66 pieces, and 70 of 200 workers (four passes with gaps)."""
+    case = wl.make_case("passes", 97, batch=len(lens), s_q=1, heads=heads, seqlens=lens)
+    assert len(lens) * heads > 16 * -(-ns // (len(lens) if flags else 1))
+    out, lse, _ = run_cpu(exe, tmp_path, case, 1, flags=flags, ns=ns)
+    check(out, lse, case)
 
 
 @pytest.mark.parametrize("variant", [0, 1, 2])

@@ -1,5 +1,5 @@
-"""The merge of partial rows where its passes and row groups have remainders: more than 64 pieces of a sequence (one lane
-each, several passes), more workers than blocks, row counts that no workgroup of four rows divides, more than 64
+"""The merge of partial rows where its passes and row groups have remainders: more than 64 pieces of a sequence (a wave takes
+64 at a time, where rows are so few that a workgroup merges each, all of them), more workers than blocks, row counts that no workgroup of four rows divides, more than 64
 sequences in the plan's sums, empty sequences.  The bounds are the ones of test_gpu_parity.py."""
 import numpy as np
 import pytest
@@ -59,3 +59,15 @@ def test_first_64_shares_without_blocks(env, heads, lens, splits, flags):
     out, lse = run_gpu(torch, amla, case, to_dev(torch, case), variant=1, num_splits=splits, flags=flags)
     want, want_lse = orc.decode(case.q_bits, case.kv_bits, case.block_table, case.seqlens, case.softmax_scale)
     check(out, lse, want, want_lse, f"late shares heads {heads} splits {splits} flags {flags}")
+
+
+@pytest.mark.parametrize("heads,lens,pieces,flags", [(128, [70 * 64 - 3] + [300] * 8, 65, 0), (48, [9000] + [0] * 9, 256, BALANCED),
+                                                     (48, [200 * 64] + [0] * 9, 200, BALANCED)])
+def test_wave_merge_of_fp16_rows_in_several_passes(env, heads, lens, pieces, flags):
+    """So many rows that a wave merges each of them: 65 pieces, 141 of 256 workers (passes with gaps), 200."""
+    torch, orc, amla, wl = env
+    case = wl.make_case("passes", 98, batch=len(lens), s_q=1, heads=heads, seqlens=lens, spare_frac=0.1)
+    assert len(lens) * heads > 16 * -(-pieces // (len(lens) if flags else 1))
+    out, lse = run_gpu(torch, amla, case, to_dev(torch, case), variant=1, num_splits=pieces, flags=flags)
+    want, want_lse = orc.decode(case.q_bits, case.kv_bits, case.block_table, case.seqlens, case.softmax_scale)
+    check(out, lse, want, want_lse, f"passes heads {heads} pieces {pieces} flags {flags}")
