@@ -42,6 +42,10 @@
  * (AMLA_FLAG_TRANSPOSED_ACC) computes both products transposed, so the rescale factor is a per-lane
  * scalar and every rescale passes over all 256 accumulator registers of the wave; it is kept as the
  * baseline in which the cost of the paper's [V2] stage shows, and carries the lazy and ldexp forms.
+ * The default runs sequences of at most 32 query rows (s_q * num_heads) in kernels of their own, in which
+ * all four waves of a workgroup work on a block: both products transposed, the value columns dealt among
+ * the waves, a rescale over all 32 or 64 accumulator registers of a wave when one of its rows moved; the
+ * reference follows the running maximum once per block, whichever variant.
  *
  * Every pointer below is a DEVICE pointer unless it says host.  amla_decode allocates no device
  * memory, never synchronises the device, reads no environment variable, and enqueues all work on
@@ -102,7 +106,9 @@ enum {
                                    per cache block.  The eight blocks are worked one after the other under
                                    the reference the iteration started with (their weights may exceed 1;
                                    a row whose maximum leaves that reference by more than 2^8 moves it at
-                                   once).  Same result up to rounding.  Default (row-rescale) kernels with
+                                   once).  Counted from a range's first block, which sets the reference,
+                                   it moves in the last block of every eight, under ADD with more than 32
+                                   query rows a sequence in the first.  Same result up to rounding.  Default (row-rescale) kernels with
                                    AMLA_RESCALE_MUL or AMLA_RESCALE_ADD only. */
   AMLA_FLAG_TRANSPOSED_ACC = 128 /* run the kernels that compute both products transposed (S^T = K Q^T,
                                    O^T = V^T P^T): the accumulator's rescale factor is then a per-lane
