@@ -72,7 +72,7 @@ struct DecodeParams {
   float scale_log2e;        // softmax_scale * log2(e)
   int32_t batch;
   int32_t rows;             // G
-  int32_t n_tiles;          // ceil(G / 128)
+  int32_t n_tiles;          // ceil(G / rows of a workgroup)
   int32_t n_splits;
   int32_t max_blocks;
   int32_t n_streams;        // batch * n_splits; balanced decomposition: number of workers
@@ -218,7 +218,7 @@ __device__ __forceinline__ BatchBlocks batch_blocks(const int32_t* seqlens, int 
 
 // Kernels defined in other translation units of the library, looked up by amla_decode.
 typedef void (*AmlaDecodeKernel)(const DecodeParams);
-AmlaDecodeKernel amla_row_rescale_kernel(int variant, bool balanced, bool iteration_512, int rows);   // amla_decode_rg.hip
+AmlaDecodeKernel amla_row_rescale_kernel(int variant, bool balanced, bool iteration_512, int tile_rows);   // amla_decode_rg.hip
 int amla_row_rescale_lds_bytes();
 
 #endif  // AMLA_DEVICE_H_
