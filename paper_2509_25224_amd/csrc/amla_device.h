@@ -82,6 +82,8 @@ struct DecodeParams {
   int32_t causal_span;      // s_q - 1 under the causal mask among the s_q query tokens, else 0
   int32_t s_q;              // query tokens per sequence in the q array
   const int32_t* q_lens;    // [B] query tokens sequence b really has (<= s_q), or null: s_q everywhere
+  int32_t* plan;            // balanced, row-rescale kernels: what the merge has to know of the plan (PlanUnits), in the workspace
+  int32_t tile_workers;     // balanced: workers where row tiles are items of the plan of their own (PlanUnits); 0: they never are
   int32_t even_xcds;        // equal shares, row-rescale kernels: every XCD an equal stretch of the workgroups, else whole sequences in turn
 };
 
@@ -191,25 +193,59 @@ __device__ __forceinline__ int lane_shift(int v) { return __builtin_amdgcn_updat
   } while (0)
 #endif
 
-// Blocks of all sequences, and this lane's part of those before sequence b (AMLA_WAVE_SUM has the sum).  Kept to a few
+// What the balanced decomposition lays end to end and cuts, the units of its plan: the cache blocks of all sequences, each range of them worked by a
+// workgroup for every row tile; or, where sequences have different numbers of tokens and a token's heads fill row tiles, the blocks of all (sequence, row tile)
+// items whose tile has rows of real tokens, tile by tile, each range worked by one workgroup.  The second leaves no workgroup with
+// padding tiles, but the tiles of a sequence no longer share its blocks in an XCD's L2, and more results are merged.  So it is taken where a quarter of the
+// (tile, block) pairs at least are padding, and sequences have eight blocks on average: every
+// workgroup decides that alike.  Tiles of 128 rows, us a
+// call (ADD), by sequence / by tile: 40 sequences of 130 .. 5000 keys, three tokens, 2/3 of the pairs real 109.2 / 104.7, all of them 113.6 /
+// 135.0; 64 of 3000 .. 4000, four, 5/8 real 244.9 / 188.7; 100 of 100 .. 2000, two, 3/4 real 107.6 / 102.8; 200 of 64 .. 300, three, 2/3 real
+// 95.5 / 97.5.
+//
+// The merge reads who met which item from the workspace: note[0] = units of the plan, [1] = whether it went by row tiles, and from [2] on two for each
+// (sequence, row tile of a workgroup): the worker that had its first block and the one that had its last.  (Worked out from the
+// lengths again, by a wave for every one or two rows, the last of the calls above took 99.0 us and not 96.2.)
+struct PlanUnits {
+  const int32_t* seqlens;
+  const int32_t* q_lens;   // null where no plan goes by tile
+  int batch, max_blocks, s_q, heads;
+};
+__device__ __forceinline__ int plan_live_tiles(const int q_len, const int s_q, const int heads) {
+  return (int)(((unsigned)(min(max(q_len, 0), s_q) * heads) + (kRowsPerWg - 1)) / kRowsPerWg);
+}
+
+// The balanced merges' arguments beside the rows.
+struct MergePlan {
+  PlanUnits units;
+  const int32_t* note;   // DecodeParams::plan
+  int rows, workers, tile_workers, n_tiles, tile_rows;
+};
+
+// Units of all sequences, by tile where `by_tile`, and this lane's part of those before sequence b (AMLA_WAVE_SUM has the sum).  Kept to a few
 // instructions: where a merge has a wave for every row, all of them do this.
-struct BatchBlocks {
+struct BatchUnits {
   int total, before;
 };
-__device__ __forceinline__ BatchBlocks batch_blocks(const int32_t* seqlens, int batch, int max_blocks, int b, int lane) {
-  BatchBlocks s = {0, 0};
-  const int most = plan_len(0x7fffffff, max_blocks, kBlock);
+__device__ __forceinline__ BatchUnits batch_units(const PlanUnits& u, const bool by_tile, int b, int lane) {
+  BatchUnits s = {0, 0};
+  const int most = plan_len(0x7fffffff, u.max_blocks, kBlock);
   constexpr int kAhead = 4;   // 256 lengths in one round trip
-  for (int c = 0; c < batch; c += 64 * kAhead) {
-    int len[kAhead];
+  for (int c = 0; c < u.batch; c += 64 * kAhead) {
+    int len[kAhead], tokens[kAhead];
+    auto load = [&](const int32_t* from, int k) { return c + 64 * k < u.batch && c + 64 * k + lane < u.batch ? from[c + 64 * k + lane] : 0; };
 #pragma unroll
-    for (int k = 0; k < kAhead; ++k) len[k] = c + 64 * k < batch && c + 64 * k + lane < batch ? seqlens[c + 64 * k + lane] : 0;
+    for (int k = 0; k < kAhead; ++k) len[k] = load(u.seqlens, k);
+    if (by_tile)
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) tokens[k] = load(u.q_lens, k);
 #pragma unroll
     for (int k = 0; k < kAhead; ++k) {
-      if (c + 64 * k >= batch) break;
-      const int nb = (int)(((unsigned)min(max(len[k], 0), most) + (kBlock - 1)) / kBlock);
-      s.total += nb;
-      s.before += c + 64 * k + lane < b ? nb : 0;
+      if (c + 64 * k >= u.batch) break;
+      int n = (int)(((unsigned)min(max(len[k], 0), most) + (kBlock - 1)) / kBlock);
+      if (by_tile) n *= plan_live_tiles(tokens[k], u.s_q, u.heads);
+      s.total += n;
+      s.before += c + 64 * k + lane < b ? n : 0;
     }
   }
   AMLA_WAVE_SUM(s.total);
