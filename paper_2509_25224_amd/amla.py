@@ -77,6 +77,7 @@ lib.amla_status_string.argtypes = [ctypes.c_int]
 
 
 _torch_module = None
+_native = None
 
 
 def _torch():
@@ -86,6 +87,16 @@ def _torch():
         import torch
         _torch_module = torch
     return _torch_module
+
+
+def _native_decode():
+    """decode() of the extension module (csrc/amla_torch.cpp), which needs torch to be loaded."""
+    global _native
+    if _native is None:
+        _torch()
+        from . import _amla_torch
+        _native = _amla_torch.decode
+    return _native
 
 
 def _current_stream(device):
@@ -136,38 +147,11 @@ def amla_decode(q, kv_cache, block_table, seqlens, softmax_scale, out=None, lse=
     `q_lens` (int32 CUDA tensor [B], optional): query tokens each sequence really has.
     The call is enqueued on torch's current stream.
     """
-    torch = _torch()
-    bf16, i32 = torch.bfloat16, torch.int32
-    if not (q.is_cuda and q.is_contiguous() and q.dtype == bf16 and kv_cache.is_cuda and kv_cache.is_contiguous() and
-            kv_cache.dtype == bf16 and block_table.is_cuda and block_table.is_contiguous() and block_table.dtype == i32 and
-            seqlens.is_cuda and seqlens.is_contiguous() and seqlens.dtype == i32):
-        raise ValueError("inputs must be contiguous CUDA tensors of the documented dtypes")
-    B, T, H, D = q.shape
-    nblk, bs, D2 = kv_cache.shape
-    if block_table.shape[0] != B or seqlens.shape[0] != B:
-        raise ValueError("block_table / seqlens batch mismatch")
-    if D2 != D:
-        raise ValueError("q and kv_cache row widths differ")
-    if q_lens is not None and not (q_lens.is_cuda and q_lens.is_contiguous() and q_lens.dtype == i32 and q_lens.shape == (B,)):
-        raise ValueError("q_lens must be a contiguous int32 CUDA tensor of shape [batch]")
-    device = q.device
-    desc = AmlaDesc(B, T, H, D, 512, bs, nblk, block_table.shape[1], int(variant), int(num_splits), int(flags), 0,
-                    None, 0, _current_stream(device), None if q_lens is None else q_lens.data_ptr())
-    ref = ctypes.byref(desc)
-    if out is None:
-        out = q.new_empty((B, T, H, 512))
-    if lse is None and want_lse:
-        lse = torch.empty((B, T, H), dtype=torch.float32, device=device)
-    need = lib.amla_workspace_bytes(ref)
-    if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
-        workspace = torch.empty(need, dtype=torch.uint8, device=device)
-    if workspace is not None:
-        desc.workspace = workspace.data_ptr()
-        desc.workspace_bytes = workspace.numel() * workspace.element_size()
-    st = lib.amla_decode(q.data_ptr(), kv_cache.data_ptr(), block_table.data_ptr(), seqlens.data_ptr(),
-                         softmax_scale, out.data_ptr(), None if lse is None else lse.data_ptr(), ref)
-    if st != AMLA_OK:
-        raise AmlaError(st)
+    decode = _native or _native_decode()
+    out, lse, status = decode(q, kv_cache, block_table, seqlens, softmax_scale, out, lse, int(variant), int(num_splits), int(flags),
+                              workspace, want_lse, q_lens)
+    if status != AMLA_OK:
+        raise AmlaError(status)
     return out, lse
 
 
