@@ -325,13 +325,13 @@ inline void acc_scale_rows(float factor) {
 }
 template <int I>
 inline void acc_exponent_add_rows(int n23) {
-  // saturating INT32 add, then the median of sum, operand and an unsigned bound (the instruction pair of the GPU build)
+  // saturating INT32 add, then max with the sign bit (the instruction pair of the GPU build)
   for (int dt = 0; dt < 16; ++dt) {
     const int i = __builtin_bit_cast(int, shim::acc_file[16 * dt + I]);
     long long r = (long long)i + n23;
     r = r > 2147483647ll ? 2147483647ll : (r < -2147483648ll ? -2147483648ll : r);
-    const unsigned sum = (unsigned)(int)r, x = (unsigned)i, up = n23 > 0 ? 0xffffffffu : 0u;
-    shim::acc_file[16 * dt + I] = __builtin_bit_cast(float, std::max(std::min(sum, x), std::min(std::max(sum, x), up)));
+    const int guard = i & (int)0x80000000;
+    shim::acc_file[16 * dt + I] = __builtin_bit_cast(float, std::max((int)r, guard));
   }
 }
 template <int I>
