@@ -8,6 +8,8 @@
 //             cache bits, block table, seqlens and, when announced, q_lens
 // output file: int32 status, int32 effective splits; then, when status is 0, out bits
 //             [batch * rows * 512] uint16 and lse [batch * rows] float
+// output file with ".info" behind its name, when status is 0: int64 row tiles of a sequence, whether the balanced plan went by row
+//             tiles (0/1), 16-byte direct-to-LDS loads issued
 #include "../../paper_2509_25224_amd/csrc/amla_decode.hip"
 #include "../../paper_2509_25224_amd/csrc/amla_decode_rg.hip"
 
@@ -74,6 +76,12 @@ int main(int argc, char** argv) {
     std::fwrite(lse, 4, n_rows, f);
   }
   std::fclose(f);
+  if (status == AMLA_OK) {
+    const long long info[3] = {shim::decode_tiles, shim::decode_plan != nullptr && shim::decode_plan[1], shim::lds_loads.load()};
+    f = std::fopen((std::string(argv[2]) + ".info").c_str(), "wb");
+    if (!f || std::fwrite(info, sizeof(info), 1, f) != 1) return 2;
+    std::fclose(f);
+  }
   std::free(q); std::free(kv); std::free(table); std::free(lens); std::free(out); std::free(lse); std::free(ws); std::free(q_lens);
   return 0;
 }

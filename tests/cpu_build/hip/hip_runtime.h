@@ -176,8 +176,10 @@ inline V4 ds_read_tr16_b64(V4* p) {
   return out;
 }
 
+inline std::atomic<long long> lds_loads{0};   // direct-to-LDS loads issued so far, one for each lane
 inline void global_load_lds(const void* g, void* lds_base, int bytes, int, int) {
   if (bytes != 16) std::abort();
+  lds_loads.fetch_add(1, std::memory_order_relaxed);
   unsigned char* dst = static_cast<unsigned char*>(lds_base) + 16 * lane;
   volatile unsigned char probe = *static_cast<const unsigned char*>(g);          // the read is checked at issue
   probe = static_cast<const unsigned char*>(g)[15];
@@ -197,6 +199,18 @@ inline void wait_tile_loads_but(int n) {
   pending->erase(pending->begin(), pending->begin() + land);
 }
 inline void syncthreads() { wg_bar->arrive_and_wait(); }
+
+// What the last decode kernel was launched with, for the harness to report: row tiles of a sequence, and where its workers
+// note the plan (null without one).
+inline int decode_tiles = 0;
+inline const int32_t* decode_plan = nullptr;
+template <class P, class... Rest>
+void record_launch(const P& p, const Rest&...) {
+  if constexpr (requires { p.plan, p.n_tiles; }) {
+    decode_tiles = p.n_tiles;
+    decode_plan = p.plan;
+  }
+}
 
 // Runs kernel(args) for every workgroup of a 1-D or 2-D grid with `threads` work-items each (a
 // multiple of 64).  Workgroups run one after another; the work-items of one run concurrently.
@@ -258,6 +272,7 @@ inline hipError_t hipGetSymbolAddress(void** ptr, const void* symbol) {
     const dim3 shim_grid = (grid), shim_block = (block);                                           \
     (void)(lds_bytes);                                                                             \
     (void)(stream);                                                                                \
+    shim::record_launch(__VA_ARGS__);                                                              \
     shim::launch(shim_grid.x, shim_grid.y, shim_block.x, [&] { kern(__VA_ARGS__); });              \
   } while (0)
 
