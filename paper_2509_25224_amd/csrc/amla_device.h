@@ -85,6 +85,7 @@ struct DecodeParams {
   int32_t* plan;            // balanced, row-rescale kernels: what the merge has to know of the plan (PlanUnits), in the workspace
   int32_t tile_workers;     // balanced: workers where row tiles are items of the plan of their own (PlanUnits); 0: they never are
   int32_t even_xcds;        // equal shares, row-rescale kernels: every XCD an equal stretch of the workgroups, else whole sequences in turn
+  int32_t early_queries;    // equal shares, tiles of 128 rows: query rows are asked for before a share is known to have blocks (QueryLoads)
 };
 
 // A row's shift that puts its limit before every key: the row of a padding token.
