@@ -200,13 +200,15 @@ inline void wait_tile_loads_but(int n) {
 }
 inline void syncthreads() { wg_bar->arrive_and_wait(); }
 
-// What the last decode kernel was launched with, for the harness to report: row tiles of a sequence, and where its workers
+// What the last decode kernel was launched with, for the harness to report: workgroups, row tiles of a sequence, and where its workers
 // note the plan (null without one).
+inline unsigned decode_grid = 0;
 inline int decode_tiles = 0;
 inline const int32_t* decode_plan = nullptr;
 template <class P, class... Rest>
-void record_launch(const P& p, const Rest&...) {
+void record_launch(unsigned grid, const P& p, const Rest&...) {
   if constexpr (requires { p.plan, p.n_tiles; }) {
+    decode_grid = grid;
     decode_tiles = p.n_tiles;
     decode_plan = p.plan;
   }
@@ -272,7 +274,7 @@ inline hipError_t hipGetSymbolAddress(void** ptr, const void* symbol) {
     const dim3 shim_grid = (grid), shim_block = (block);                                           \
     (void)(lds_bytes);                                                                             \
     (void)(stream);                                                                                \
-    shim::record_launch(__VA_ARGS__);                                                              \
+    shim::record_launch(shim_grid.x, __VA_ARGS__);                                                 \
     shim::launch(shim_grid.x, shim_grid.y, shim_block.x, [&] { kern(__VA_ARGS__); });              \
   } while (0)
 

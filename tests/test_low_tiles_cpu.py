@@ -10,7 +10,7 @@ LOADS_OF_A_BLOCK = 64 * 72   # 16-byte loads
 
 
 def launch_info(tmp_path):
-    """Row tiles of a sequence, whether the balanced plan went by row tiles, direct-to-LDS loads of run_cpu's last call."""
+    """Row tiles of a sequence, whether the balanced plan went by row tiles, direct-to-LDS loads, workgroups of run_cpu's last call."""
     return (int(x) for x in np.fromfile(str(tmp_path / "out.bin.info"), np.int64))
 
 
@@ -24,6 +24,6 @@ def test_low_tiles_of_padding_tokens(exe, tmp_path, heads, columns, tile_rows, v
         case = wl.make_case("low_padding", 106, batch=batch, s_q=4, heads=heads, seqlens=part, max_blocks_per_seq=columns, spare_frac=0.2)
         out, lse, _ = run_cpu(exe, tmp_path, case, variant, flags=flags, q_lens=tokens)
         check(out, lse, case, causal=flags == CAUSAL, q_lens=tokens)
-        tiles, _, loads = launch_info(tmp_path)
+        tiles, _, loads, _ = launch_info(tmp_path)
         assert tiles == -(-4 * heads // tile_rows)
         assert loads == LOADS_OF_A_BLOCK * sum(-(-n // 64) * -(-t * heads // tile_rows) for n, t in zip(part, tokens))
