@@ -204,7 +204,7 @@ __device__ __forceinline__ int lane_shift(int v) { return __builtin_amdgcn_updat
 // 135.0; 64 of 3000 .. 4000, four, 5/8 real 244.9 / 188.7; 100 of 100 .. 2000, two, 3/4 real 107.6 / 102.8; 200 of 64 .. 300, three, 2/3 real
 // 95.5 / 97.5.
 //
-// The merge reads who met which item from the workspace: note[0] = units of the plan, [1] = whether it went by row tiles, and from [2] on two for each
+// The merge reads who met which item from the workspace: note[0] = whether the plan went by row tiles, and from [1] on two for each
 // (sequence, row tile of a workgroup): the worker that had its first block and the one that had its last.  (Worked out from the
 // lengths again, by a wave for every one or two rows, the last of the calls above took 99.0 us and not 96.2.)
 struct PlanUnits {
@@ -220,7 +220,7 @@ __device__ __forceinline__ int plan_live_tiles(const int q_len, const int s_q, c
 struct MergePlan {
   PlanUnits units;
   const int32_t* note;   // DecodeParams::plan
-  int rows, workers, tile_workers, n_tiles, tile_rows;
+  int rows, workers, n_tiles, tile_rows;
 };
 
 // Units of all sequences, by tile where `by_tile`, and this lane's part of those before sequence b (AMLA_WAVE_SUM has the sum).  Kept to a few

@@ -9,7 +9,8 @@
 // output file: int32 status, int32 effective splits; then, when status is 0, out bits
 //             [batch * rows * 512] uint16 and lse [batch * rows] float
 // output file with ".info" behind its name, when status is 0: int64 row tiles of a sequence, whether the balanced plan went by row
-//             tiles (0/1), 16-byte direct-to-LDS loads issued, workgroups of the decode kernel
+//             tiles (0/1), 16-byte direct-to-LDS loads issued, workgroups of the decode kernel; then, where the workers noted their plan,
+//             int32 first and last worker of every (sequence, row tile)
 #include "../../paper_2509_25224_amd/csrc/amla_decode.hip"
 #include "../../paper_2509_25224_amd/csrc/amla_decode_rg.hip"
 
@@ -77,10 +78,11 @@ int main(int argc, char** argv) {
   }
   std::fclose(f);
   if (status == AMLA_OK) {
-    const long long info[4] = {shim::decode_tiles, shim::decode_plan != nullptr && shim::decode_plan[1], shim::lds_loads.load(),
+    const long long info[4] = {shim::decode_tiles, shim::decode_plan != nullptr && shim::decode_plan[0], shim::lds_loads.load(),
                                shim::decode_grid};
     f = std::fopen((std::string(argv[2]) + ".info").c_str(), "wb");
     if (!f || std::fwrite(info, sizeof(info), 1, f) != 1) return 2;
+    if (shim::decode_plan != nullptr) std::fwrite(shim::decode_plan + 1, 4, (size_t)2 * d.batch * shim::decode_tiles, f);
     std::fclose(f);
   }
   std::free(q); std::free(kv); std::free(table); std::free(lens); std::free(out); std::free(lse); std::free(ws); std::free(q_lens);

@@ -6,6 +6,7 @@ import pytest
 
 from paper_2509_25224_amd import workloads as wl
 from test_cpu_build import ADD, BALANCED, CAUSAL, COMP, MUL, check, exe, run_cpu  # noqa: F401
+from test_low_tiles_cpu import launch_info
 
 
 @pytest.mark.parametrize("heads,s_q,lens,q_lens,workers,variant,flags,static", [
@@ -22,3 +23,18 @@ def test_plans_by_tile_and_by_sequence(exe, tmp_path, heads, s_q, lens, q_lens, 
     check(out, lse, case, causal=bool(flags & CAUSAL), q_lens=q_lens)
     for b, k in enumerate(q_lens):
         assert np.all(out[b, k:] == 0) and np.all(np.isneginf(lse[b, k:]))
+
+
+@pytest.mark.parametrize("heads,lens,workers,variant", [(20, [200, 0, 64, 330], 23, ADD), (130, [64, 700], 200, MUL), (2, [900], 256, COMP)])
+def test_workers_are_numbered_without_gaps(exe, tmp_path, heads, lens, workers, variant):
+    """More workers than blocks: a block each for as many as there are blocks, and those of a sequence side by side for the merge."""
+    case = wl.make_case("no_gaps", 109, batch=len(lens), s_q=1, heads=heads, seqlens=lens, spare_frac=0.2)
+    out, lse, _ = run_cpu(exe, tmp_path, case, variant, flags=BALANCED, ns=workers)
+    check(out, lse, case)
+    tiles, by_tile, _, _ = launch_info(tmp_path)
+    notes = np.fromfile(str(tmp_path / "out.bin.info"), np.int32, offset=32).reshape(len(lens), tiles, 2)
+    before = 0
+    for b, n in enumerate(lens):
+        blocks = -(-n // 64)
+        assert not by_tile and (blocks == 0 or np.all(notes[b] == [before, before + blocks - 1]))
+        before += blocks
