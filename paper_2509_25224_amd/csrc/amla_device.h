@@ -198,8 +198,10 @@ __device__ __forceinline__ int lane_shift(int v) { return __builtin_amdgcn_updat
 // workgroup for every row tile; or, where sequences have different numbers of tokens and a token's heads fill row tiles, the blocks of all (sequence, row tile)
 // items whose tile has rows of real tokens, tile by tile, each range worked by one workgroup.  The second leaves no workgroup with
 // padding tiles, but the tiles of a sequence no longer share its blocks in an XCD's L2, and more results are merged.  So it is taken where a quarter of the
-// (tile, block) pairs at least are padding, and sequences have eight blocks on average: every
-// workgroup decides that alike.  Tiles of 128 rows, us a
+// (tile, block) pairs at least are padding, sequences have eight blocks on average and every worker two units: every
+// workgroup decides that alike.  (With fewer units the decode kernel has little to gain, and twice as many pieces are merged: 2 sequences of three
+// tokens, one real, 1.3 units a worker, 42.6 / 51.5; 4 of two tokens and 9600 keys 38.2 / 44.1.  With these conditions the plan is the faster one, or
+// at most 3 % slower, in all of 300 shapes of 1 .. 256 sequences, two to four row tiles and 3 .. 500 blocks; they are 1.10 times as fast as by sequence.)  Tiles of 128 rows, us a
 // call (ADD), by sequence / by tile: 40 sequences of 130 .. 5000 keys, three tokens, 2/3 of the pairs real 109.2 / 104.7, all of them 113.6 /
 // 135.0; 64 of 3000 .. 4000, four, 5/8 real 244.9 / 188.7; 100 of 100 .. 2000, two, 3/4 real 107.6 / 102.8; 200 of 64 .. 300, three, 2/3 real
 // 95.5 / 97.5.

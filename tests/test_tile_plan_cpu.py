@@ -1,5 +1,5 @@
 """Per-sequence token counts in the CPU build (see test_cpu_build.py): the balanced plan goes by row tiles where a quarter of the (tile, block) pairs are
-padding and sequences have eight blocks on average, else by sequences; the workspace of exactly the documented size holds either one's pieces
+padding, sequences have eight blocks on average and workers two units, else by sequences; the workspace of exactly the documented size holds either one's pieces
 and notes."""
 import numpy as np
 import pytest
@@ -9,18 +9,23 @@ from test_cpu_build import ADD, BALANCED, CAUSAL, COMP, MUL, check, exe, run_cpu
 from test_low_tiles_cpu import launch_info
 
 
-@pytest.mark.parametrize("heads,s_q,lens,q_lens,workers,variant,flags,static", [
-    (65, 2, [700, 0, 520, 580], [1, 2, 2, 0], 1, ADD, CAUSAL, False),      # two tiles, the last of two rows; one worker a tile
-    (65, 2, [700, 0, 520, 580], [1, 2, 2, 0], 40, MUL, CAUSAL, True),      # more workers than units
-    (129, 1, [1200, 513], [0, 1], 3, COMP, BALANCED, False),               # a tile of one row; a sequence of many keys without tokens
-    (128, 2, [512, 511], [1, 2], 2, ADD, CAUSAL, False),                   # 24 of 32 pairs: by tile
-    (128, 2, [576, 512], [2, 1], 2, ADD, CAUSAL, False),                   # 26 of 34: by sequence
-    (128, 2, [512, 448], [1, 1], 2, ADD, CAUSAL, False),                   # 15 blocks of two sequences: by sequence
-    (129, 1, [600], [1], 1, MUL, BALANCED, False)])                        # the smallest workspace of two tiles: two slots' worth
-def test_plans_by_tile_and_by_sequence(exe, tmp_path, heads, s_q, lens, q_lens, workers, variant, flags, static):
+@pytest.mark.parametrize("heads,s_q,lens,q_lens,workers,variant,flags,static,by_tile", [
+    (65, 2, [700, 64, 1000, 580], [1, 2, 2, 0], 1, ADD, CAUSAL, False, True),     # two tiles, the last of two rows; one worker a tile
+    (65, 2, [700, 64, 1000, 580], [1, 2, 2, 0], 40, MUL, CAUSAL, True, False),    # more workers than units
+    (65, 2, [700, 0, 520, 580], [1, 2, 2, 0], 1, COMP, CAUSAL, False, False),     # 30 blocks of four sequences
+    (129, 1, [1200, 513], [0, 1], 3, COMP, BALANCED, False, True),                # a tile of one row; a sequence of many keys without tokens
+    (128, 2, [512, 511], [1, 2], 2, ADD, CAUSAL, False, True),                    # 24 of 32 pairs
+    (128, 2, [512, 511], [1, 2], 6, ADD, CAUSAL, True, True),                     # two units for each of twelve workers
+    (128, 2, [512, 511], [1, 2], 7, MUL, CAUSAL, False, False),                   # less
+    (128, 2, [576, 512], [2, 1], 2, ADD, CAUSAL, False, False),                   # 26 of 34 pairs
+    (128, 2, [512, 448], [1, 1], 2, ADD, CAUSAL, False, False),                   # 15 blocks of two sequences
+    (129, 1, [600], [1], 1, MUL, BALANCED, False, False)])                        # the smallest workspace of two tiles: two slots' worth
+def test_plans_by_tile_and_by_sequence(exe, tmp_path, heads, s_q, lens, q_lens, workers, variant, flags, static, by_tile):
     case = wl.make_case("tile_plan", 103, batch=len(lens), s_q=s_q, heads=heads, seqlens=lens, spare_frac=0.2)
     out, lse, _ = run_cpu(exe, tmp_path, case, variant, flags=flags, ns=workers, q_lens=q_lens, static_ws=static)
     check(out, lse, case, causal=bool(flags & CAUSAL), q_lens=q_lens)
+    tiles, went_by_tile, _, _ = launch_info(tmp_path)
+    assert tiles == 2 and went_by_tile == by_tile
     for b, k in enumerate(q_lens):
         assert np.all(out[b, k:] == 0) and np.all(np.isneginf(lse[b, k:]))
 
