@@ -83,7 +83,8 @@ struct DecodeParams {
   int32_t s_q;              // query tokens per sequence in the q array
   const int32_t* q_lens;    // [B] query tokens sequence b really has (<= s_q), or null: s_q everywhere
   int32_t* plan;            // balanced, row-rescale kernels: what the merge has to know of the plan (PlanUnits), in the workspace
-  int32_t tile_workers;     // balanced: workers where row tiles are items of the plan of their own (PlanUnits); 0: they never are
+  int32_t tile_workers;     // balanced: workers where row tiles are items of the plan of their own (PlanUnits); 0: they are not in this call
+  int32_t tile_shift;       // log2 of a workgroup's rows
   int32_t even_xcds;        // equal shares, row-rescale kernels: every XCD an equal stretch of the workgroups, else whole sequences in turn
   int32_t early_queries;    // equal shares, tiles of 128 rows: query rows are asked for before a share is known to have blocks (QueryLoads)
 };
@@ -195,16 +196,18 @@ __device__ __forceinline__ int lane_shift(int v) { return __builtin_amdgcn_updat
 #endif
 
 // What the balanced decomposition lays end to end and cuts, the units of its plan: the cache blocks of all sequences, each range of them worked by a
-// workgroup for every row tile; or, where sequences have different numbers of tokens and a token's heads fill row tiles, the blocks of all (sequence, row tile)
-// items whose tile has rows of real tokens, tile by tile, each range worked by one workgroup.  The second leaves no workgroup with
-// padding tiles, but the tiles of a sequence no longer share its blocks in an XCD's L2, and more results are merged.  So it is taken where a quarter of the
-// (tile, block) pairs at least are padding, sequences have eight blocks on average and every worker two units: every
-// workgroup decides that alike.  (With fewer units the decode kernel has little to gain, and twice as many pieces are merged: 2 sequences of three
-// tokens, one real, 1.3 units a worker, 42.6 / 51.5; 4 of two tokens and 9600 keys 38.2 / 44.1.  With these conditions the plan is the faster one, or
-// at most 3 % slower, in all of 300 shapes of 1 .. 256 sequences, two to four row tiles and 3 .. 500 blocks; they are 1.10 times as fast as by sequence.)  Tiles of 128 rows, us a
-// call (ADD), by sequence / by tile: 40 sequences of 130 .. 5000 keys, three tokens, 2/3 of the pairs real 109.2 / 104.7, all of them 113.6 /
-// 135.0; 64 of 3000 .. 4000, four, 5/8 real 244.9 / 188.7; 100 of 100 .. 2000, two, 3/4 real 107.6 / 102.8; 200 of 64 .. 300, three, 2/3 real
-// 95.5 / 97.5.
+// workgroup for every row tile; or, where sequences have different numbers of tokens, the blocks of all (sequence, row tile) items whose tile has
+// rows of real tokens, tile by tile, each range worked by one workgroup.  The second leaves no workgroup with padding tiles, but the tiles of a
+// sequence no longer share its blocks in an XCD's L2, and more results are merged.  So it is taken where a quarter of the (tile, block) pairs at
+// least are padding and the workers' ranges are long enough for that; every workgroup decides alike.
+//   Tiles of 128 rows: sequences have eight blocks on average, workers two units, or one and a half where that is two less than by sequence.  us a call
+// (ADD), by sequence / by tile: 40 sequences of 130 .. 5000 keys, three tokens, 2/3 of the pairs real 109.2 / 104.7, all of them 113.6 / 135.0; 64 of 3000 ..
+// 4000, four, 5/8 real 244.9 / 188.7; 100 of 100 .. 2000, two, 3/4 real 107.6 / 102.8; 200 of 64 .. 300, three, 2/3 real 95.5 / 97.5; 2 of three
+// tokens, one real, 1.3 units a worker 42.6 / 51.5.  Of 300 shapes of 1 .. 256 sequences, two to four row tiles and 3 .. 500 blocks no call that takes it is
+// more than 3 % slower than before there was a choice.
+//   Tiles of 16 and 32 rows: ranges are shorter by a block and a half.  (The blocks and the merge take half as long, and no more workgroups than one round
+// holds are there to fill.)  60 sequences of two tokens of 64 heads, one real, 32.3 / 27.3; 3 of four of 128, up to two real, 30.8 / 23.1; 7 of three, two
+// real, 32.1 / 35.4.  Of 300 shapes 60 take it: 1.06 times as fast.
 //
 // The merge reads who met which item from the workspace: note[0] = whether the plan went by row tiles, and from [1] on two for each
 // (sequence, row tile of a workgroup): the worker that had its first block and the one that had its last.  (Worked out from the
@@ -212,26 +215,27 @@ __device__ __forceinline__ int lane_shift(int v) { return __builtin_amdgcn_updat
 struct PlanUnits {
   const int32_t* seqlens;
   const int32_t* q_lens;   // null where no plan goes by tile
-  int batch, max_blocks, s_q, heads;
+  int batch, max_blocks, s_q, heads, tile_shift;
+  // row tiles with rows of real tokens
+  __device__ __forceinline__ int live_tiles(const int q_len) const {
+    return (int)(((unsigned)(min(max(q_len, 0), s_q) * heads) + (1u << tile_shift) - 1) >> tile_shift);
+  }
 };
-__device__ __forceinline__ int plan_live_tiles(const int q_len, const int s_q, const int heads) {
-  return (int)(((unsigned)(min(max(q_len, 0), s_q) * heads) + (kRowsPerWg - 1)) / kRowsPerWg);
-}
 
 // The balanced merges' arguments beside the rows.
 struct MergePlan {
   PlanUnits units;
   const int32_t* note;   // DecodeParams::plan
-  int rows, workers, n_tiles, tile_rows;
+  int rows, workers, n_tiles;
 };
 
-// Units of all sequences, by tile where `by_tile`, and this lane's part of those before sequence b (AMLA_WAVE_SUM has the sum).  Kept to a few
-// instructions: where a merge has a wave for every row, all of them do this.
+// Blocks of all sequences, units by tile too where `by_tile`, and this lane's part of the blocks before sequence b (AMLA_WAVE_SUM has the sum).  Kept to a
+// few instructions: this stands before a workgroup's first load.
 struct BatchUnits {
-  int total, before;
+  int blocks, tiled, before;
 };
 __device__ __forceinline__ BatchUnits batch_units(const PlanUnits& u, const bool by_tile, int b, int lane) {
-  BatchUnits s = {0, 0};
+  BatchUnits s = {0, 0, 0};
   const int most = plan_len(0x7fffffff, u.max_blocks, kBlock);
   constexpr int kAhead = 4;   // 256 lengths in one round trip
   for (int c = 0; c < u.batch; c += 64 * kAhead) {
@@ -245,19 +249,20 @@ __device__ __forceinline__ BatchUnits batch_units(const PlanUnits& u, const bool
 #pragma unroll
     for (int k = 0; k < kAhead; ++k) {
       if (c + 64 * k >= u.batch) break;
-      int n = (int)(((unsigned)min(max(len[k], 0), most) + (kBlock - 1)) / kBlock);
-      if (by_tile) n *= plan_live_tiles(tokens[k], u.s_q, u.heads);
-      s.total += n;
+      const int n = (int)(((unsigned)min(max(len[k], 0), most) + (kBlock - 1)) / kBlock);
+      s.blocks += n;
+      if (by_tile) s.tiled += n * u.live_tiles(tokens[k]);
       s.before += c + 64 * k + lane < b ? n : 0;
     }
   }
-  AMLA_WAVE_SUM(s.total);
+  AMLA_WAVE_SUM(s.blocks);
+  if (by_tile) AMLA_WAVE_SUM(s.tiled);
   return s;
 }
 
 // Kernels defined in other translation units of the library, looked up by amla_decode.
 typedef void (*AmlaDecodeKernel)(const DecodeParams);
-AmlaDecodeKernel amla_row_rescale_kernel(int variant, bool balanced, bool iteration_512, int tile_rows);   // amla_decode_rg.hip
+AmlaDecodeKernel amla_row_rescale_kernel(int variant, bool balanced, bool iteration_512, int tile_rows, bool by_tile);   // amla_decode_rg.hip
 int amla_row_rescale_lds_bytes();
 
 #endif  // AMLA_DEVICE_H_

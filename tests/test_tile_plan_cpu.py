@@ -43,3 +43,20 @@ def test_workers_are_numbered_without_gaps(exe, tmp_path, heads, lens, workers, 
         blocks = -(-n // 64)
         assert not by_tile and (blocks == 0 or np.all(notes[b] == [before, before + blocks - 1]))
         before += blocks
+
+
+@pytest.mark.parametrize("heads,s_q,lens,q_lens,columns,tile_rows,variant,flags,static,by_tile", [
+    (32, 16, [20 * 64 - 3], [1], 32, 16, ADD, CAUSAL, False, True),               # 8 workers by sequence: 2.5 blocks each, or 40 units for 256
+    (32, 16, [12 * 64], [1], 32, 16, MUL, CAUSAL, True, False),                   # 1.5 blocks less 24 / 256 of a unit
+    (32, 12, [25 * 64, 20 * 64 - 1], [1, 2], 47, 32, COMP, BALANCED, True, True),   # 21 workers by sequence, 252 by tile
+    (33, 12, [1500, 0, 1000], [2, 5, 0], 32, 16, MUL, CAUSAL, False, True),       # tokens that share tiles; the last tile of twelve rows
+    (33, 12, [700, 0, 300], [2, 5, 1], 32, 16, ADD, CAUSAL, False, False)])
+def test_plans_on_low_tiles(exe, tmp_path, heads, s_q, lens, q_lens, columns, tile_rows, variant, flags, static, by_tile):
+    """The library's own number of workers, on lower tiles: by row tile where that makes ranges shorter by a block and a half."""
+    case = wl.make_case("low_tile_plan", 110, batch=len(lens), s_q=s_q, heads=heads, seqlens=lens, spare_frac=0.2, max_blocks_per_seq=columns)
+    out, lse, _ = run_cpu(exe, tmp_path, case, variant, flags=flags, q_lens=q_lens, static_ws=static)
+    check(out, lse, case, causal=bool(flags & CAUSAL), q_lens=q_lens)
+    tiles, went_by_tile, _, _ = launch_info(tmp_path)
+    assert tiles == -(-s_q * heads // tile_rows) and went_by_tile == by_tile
+    for b, k in enumerate(q_lens):
+        assert np.all(out[b, k:] == 0) and np.all(np.isneginf(lse[b, k:]))
