@@ -75,3 +75,17 @@ def test_values_beyond_fp16(exe, tmp_path, heads, keys):
     for variant in (MUL, ADD, COMP):
         out, _, splits = run_cpu(exe, tmp_path, case, variant)
         assert splits == 1 and np.all(np.abs(out[..., :2] / wl.bf16_bits_to_f32(bits) - 1) <= 2.0 ** -8), (variant, out[0, 0, 0, :2])
+
+
+@pytest.mark.parametrize("rows", [33, 64, 96, 128, 256, 384, 512])
+def test_fewer_balanced_workers_are_two_for_every_sequence(rows):
+    """One workgroup per compute unit, or fewer on lower row tiles, but then at least two for every sequence."""
+    s_q, heads = (rows // 128, 128) if rows % 128 == 0 else (1, rows)
+    fewer = 0
+    for batch in range(1, 65):
+        for blocks in (4, 6, 7, 10, 16, 32, 47, 64, 125):
+            workers = amla.amla_effective_splits(amla.make_desc(batch, s_q, heads, 20000, blocks, flags=amla.AMLA_FLAG_CAUSAL))
+            most = min(256 // -(-rows // 128), batch * blocks)
+            assert workers == most or 2 * batch <= workers < most
+            fewer += workers < most
+    assert fewer > 0
