@@ -20,7 +20,7 @@ def test_query_rows_of_shares_without_blocks(exe, tmp_path, shares, asking):
 
 
 @pytest.mark.parametrize("heads,lens,flags,ns,tiles,workgroups", [
-    (128, [64, 1], 0, 27, 1, 2 * 27), (128, [64], BALANCED, 40, 1, 40),                     # a block at most: the library's own is no cut
+    (128, [64, 1], 0, 35, 1, 2 * 35), (128, [64, 1], 0, 27, 4, 2 * 27 * 4), (128, [64], BALANCED, 70, 1, 70),   # a block at most: the library's own is no cut
     (24, [50 * 64 - 7, 640], 0, 100, 2, 2 * 50 * 2), (100, [320, 30], BALANCED, 200, 7, 10 * 7),   # a block each: launched as that
     (24, [450, 576], 0, 100, 1, 2 * 100)])                                                   # the library would not cut these
 def test_more_shares_than_blocks(exe, tmp_path, heads, lens, flags, ns, tiles, workgroups):
