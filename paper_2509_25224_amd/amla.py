@@ -1,8 +1,9 @@
-"""ctypes binding of the C-ABI library (`include/amla.h`): argument marshalling only.
+"""Binding of the C-ABI library (`include/amla.h`): argument marshalling only, with ctypes, and for `amla_decode` in an
+extension module (csrc/amla_torch.cpp, `_amla_torch.so`).
 
 Every step of the decode path runs in the HIP kernels inside `libamla.so`; PyTorch is used
 for device memory and the stream handle.  There is no CPU or PyTorch fallback: importing
-this module raises if the library has not been built (run `__graft_entry__.build()`).
+this module raises if one of the two has not been built (run `__graft_entry__.build()`, with the torch it is used with).
 """
 from __future__ import annotations
 
@@ -10,6 +11,7 @@ import ctypes
 import os
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libamla.so")
+_TORCH_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_amla_torch.so")
 
 AMLA_OK = 0
 AMLA_ERR_NULL_ARG = -1
@@ -44,9 +46,10 @@ class AmlaDesc(ctypes.Structure):
     ]
 
 
-if not os.path.exists(_LIB_PATH):
-    raise ImportError(f"{_LIB_PATH} is missing: build it with __graft_entry__.build() "
-                      "(hipcc --offload-arch=gfx950); there is no fallback path")
+for _path in (_LIB_PATH, _TORCH_PATH):
+    if not os.path.exists(_path):
+        raise ImportError(f"{_path} is missing: build it with __graft_entry__.build() "
+                          "(hipcc --offload-arch=gfx950); there is no fallback path")
 
 lib = ctypes.CDLL(_LIB_PATH)
 lib.amla_decode.restype = ctypes.c_int

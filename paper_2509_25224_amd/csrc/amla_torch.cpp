@@ -17,15 +17,26 @@ namespace {
 
 bool given(PyObject* o) { return o != Py_None; }
 
-const at::Tensor& tensor(PyObject* o) {
-  if (!THPVariable_Check(o)) refuse(PyExc_TypeError, "a torch.Tensor is wanted");
-  return THPVariable_Unpack(o);
+// (what reading `attribute` of another object raises)
+const at::Tensor& tensor(PyObject* o, const char* attribute) {
+  if (THPVariable_Check(o)) return THPVariable_Unpack(o);
+  PyErr_Format(PyExc_AttributeError, "'%.200s' object has no attribute '%s': a torch.Tensor is wanted", Py_TYPE(o)->tp_name, attribute);
+  throw python_error();
 }
 
 int32_t int32(PyObject* o) {   // (as a ctypes field takes it)
   const unsigned long v = PyLong_AsUnsignedLongMask(o);
   if (v == (unsigned long)-1 && PyErr_Occurred()) throw python_error();
   return (int32_t)v;
+}
+
+float scale_of(PyObject* o) {   // (as a ctypes argument takes it)
+  const double v = PyFloat_AsDouble(o);
+  if (v != -1.0 || !PyErr_Occurred()) return (float)v;
+  PyErr_Clear();
+  THPObjectPtr ctypes(PyImport_ImportModule("ctypes")), error(ctypes ? PyObject_GetAttrString(ctypes.get(), "ArgumentError") : nullptr);
+  if (error) PyErr_SetString(error.get(), "softmax_scale: a float is wanted");
+  throw python_error();
 }
 
 bool usable(const at::Tensor& t, at::ScalarType type) { return t.is_cuda() && t.is_contiguous() && t.scalar_type() == type; }
@@ -39,19 +50,23 @@ void sized(const at::Tensor& t, int64_t n) {
 PyObject* decode(PyObject*, PyObject* const* args, Py_ssize_t n_args) {
   HANDLE_TH_ERRORS
   if (n_args != 13) refuse(PyExc_TypeError, "13 arguments are wanted");
-  const at::Tensor &q = tensor(args[0]), &kv = tensor(args[1]), &table = tensor(args[2]), &seqlens = tensor(args[3]);
-  if (!usable(q, at::kBFloat16) || !usable(kv, at::kBFloat16) || !usable(table, at::kInt) || !usable(seqlens, at::kInt))
-    refuse(PyExc_ValueError, "inputs must be contiguous CUDA tensors of the documented dtypes");
+  auto input = [&](int k, at::ScalarType type) -> const at::Tensor& {
+    const at::Tensor& t = tensor(args[k], "is_cuda");
+    if (!usable(t, type)) refuse(PyExc_ValueError, "inputs must be contiguous CUDA tensors of the documented dtypes");
+    return t;
+  };
+  const at::Tensor& q = input(0, at::kBFloat16);
+  const at::Tensor& kv = input(1, at::kBFloat16);
+  const at::Tensor& table = input(2, at::kInt);
+  const at::Tensor& seqlens = input(3, at::kInt);
   sized(q, 4);
   sized(kv, 3);
   const int64_t batch = q.size(0), s_q = q.size(1), heads = q.size(2);
   if (table.size(0) != batch || seqlens.size(0) != batch) refuse(PyExc_ValueError, "block_table / seqlens batch mismatch");
   if (kv.size(2) != q.size(3)) refuse(PyExc_ValueError, "q and kv_cache row widths differ");
-  const double scale = PyFloat_AsDouble(args[4]);
-  if (scale == -1.0 && PyErr_Occurred()) throw python_error();
   const bool has_q_lens = given(args[12]);
   if (has_q_lens) {
-    const at::Tensor& t = tensor(args[12]);
+    const at::Tensor& t = tensor(args[12], "is_cuda");
     if (!usable(t, at::kInt) || t.dim() != 1 || t.size(0) != batch)
       refuse(PyExc_ValueError, "q_lens must be a contiguous int32 CUDA tensor of shape [batch]");
   }
@@ -68,15 +83,18 @@ PyObject* decode(PyObject*, PyObject* const* args, Py_ssize_t n_args) {
   d.num_splits = int32(args[8]);
   d.flags = int32(args[9]);
   d.stream = c10::hip::getCurrentHIPStream(q.device().index()).stream();
-  d.q_lens = has_q_lens ? static_cast<const int32_t*>(tensor(args[12]).data_ptr()) : nullptr;
+  d.q_lens = has_q_lens ? static_cast<const int32_t*>(tensor(args[12], "data_ptr").data_ptr()) : nullptr;
 
-  const at::Tensor out = given(args[5]) ? tensor(args[5]) : at::empty({batch, s_q, heads, 512}, q.options());
+  const at::Tensor out = given(args[5]) ? tensor(args[5], "data_ptr") : at::empty({batch, s_q, heads, 512}, q.options());
   at::Tensor lse, workspace;
-  if (given(args[6]))
-    lse = tensor(args[6]);
-  else if (PyObject_IsTrue(args[11]) == 1)
-    lse = at::empty({batch, s_q, heads}, q.options().dtype(at::kFloat));
-  if (given(args[10])) workspace = tensor(args[10]);
+  if (given(args[6])) {
+    lse = tensor(args[6], "data_ptr");
+  } else {
+    const int want_lse = PyObject_IsTrue(args[11]);
+    if (want_lse < 0) throw python_error();
+    if (want_lse) lse = at::empty({batch, s_q, heads}, q.options().dtype(at::kFloat));
+  }
+  if (given(args[10])) workspace = tensor(args[10], "data_ptr");
   const size_t need = amla_workspace_bytes(&d);
   if (need > 0 && (!workspace.defined() || workspace.nbytes() < need)) workspace = at::empty({(int64_t)need}, q.options().dtype(at::kByte));
   if (workspace.defined()) {
@@ -87,10 +105,11 @@ PyObject* decode(PyObject*, PyObject* const* args, Py_ssize_t n_args) {
   const int32_t *table_at = static_cast<const int32_t*>(table.data_ptr()), *seqlens_at = static_cast<const int32_t*>(seqlens.data_ptr());
   void* const out_at = out.data_ptr();
   float* const lse_at = lse.defined() ? static_cast<float*>(lse.data_ptr()) : nullptr;
+  const float scale = scale_of(args[4]);
   int status;
   {
     pybind11::gil_scoped_release others_may_run;
-    status = amla_decode(q_at, kv_at, table_at, seqlens_at, (float)scale, out_at, lse_at, &d);
+    status = amla_decode(q_at, kv_at, table_at, seqlens_at, scale, out_at, lse_at, &d);
   }
   THPObjectPtr out_obj(THPVariable_Wrap(out)), lse_obj(lse.defined() ? THPVariable_Wrap(lse) : (Py_INCREF(Py_None), Py_None));
   if (!out_obj || !lse_obj) throw python_error();

@@ -1,4 +1,11 @@
-"""amla_decode's arguments on their way through the native binding: what it refuses, with which error, before anything touches a GPU."""
+"""amla_decode's arguments on their way through the native binding: what it refuses, with which error, before anything touches a GPU; and
+that both built objects are asked for at import."""
+import ctypes
+import os
+import shutil
+import subprocess
+import sys
+
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -11,10 +18,25 @@ def test_host_tensors_and_other_objects_are_refused():
     table, lens = torch.zeros(1, 4, dtype=torch.int32), torch.zeros(1, dtype=torch.int32)
     with pytest.raises(ValueError, match="contiguous CUDA tensors"):
         amla.amla_decode(q, kv, table, lens, 0.1)
-    with pytest.raises((TypeError, AttributeError)):
+    with pytest.raises(AttributeError, match="is_cuda"):
         amla.amla_decode(None, kv, table, lens, 0.1)
+    with pytest.raises(ValueError, match="contiguous CUDA tensors"):   # the first argument that is wrong is the one that is named
+        amla.amla_decode(q, None, table, lens, 0.1)
     with pytest.raises((TypeError, ValueError)):
         amla.amla_decode(q, kv, table, lens, 0.1, variant="add")
+
+
+@pytest.mark.parametrize("missing", ["libamla.so", "_amla_torch.so"])
+def test_import_asks_for_both_objects(tmp_path, missing):
+    package = os.path.dirname(os.path.abspath(amla.__file__))
+    copy = tmp_path / "paper_2509_25224_amd"
+    copy.mkdir()
+    for name in ("__init__.py", "amla.py", "libamla.so", "_amla_torch.so"):
+        if name != missing:
+            shutil.copy(os.path.join(package, name), copy / name)
+    run = subprocess.run([sys.executable, "-c", "import paper_2509_25224_amd.amla"], cwd=tmp_path, capture_output=True, text=True,
+                         env=dict(os.environ, PYTHONPATH=str(tmp_path)))
+    assert run.returncode != 0 and "ImportError" in run.stderr and missing + " is missing" in run.stderr
 
 
 @pytest.mark.gpu
@@ -38,6 +60,13 @@ def test_what_device_calls_refuse_and_return():
             amla.amla_decode(q, kv, table, lens, 0.1, **kw)
     with pytest.raises(amla.AmlaError):
         amla.amla_decode(q, kv, table, lens, float("nan"))
+    with pytest.raises(ctypes.ArgumentError):
+        amla.amla_decode(q, kv, table, lens, "0.1")
+    for kw in ({"q_lens": 3}, {"out": 3}, {"lse": 3}, {"workspace": 3}):
+        with pytest.raises(AttributeError):
+            amla.amla_decode(q, kv, table, lens, 0.1, **kw)
+    with pytest.raises(RuntimeError, match="ambiguous"):   # no truth value
+        amla.amla_decode(q, kv, table, lens, 0.1, want_lse=torch.zeros(2))
     out, lse = torch.empty(2, 1, 16, 512, dtype=torch.bfloat16, device=dev), torch.empty(2, 1, 16, device=dev)
     got = amla.amla_decode(q, kv, table, lens, 0.1, out, lse, num_splits=2, workspace=torch.empty(1, dtype=torch.uint8, device=dev))
     assert got[0] is out and got[1] is lse
