@@ -3,8 +3,8 @@ of more shares or workers than blocks, which are cut like the library's own, are
 import pytest
 
 from paper_2509_25224_amd import workloads as wl
-from test_cpu_build import ADD, BALANCED, MUL, check, exe, run_cpu  # noqa: F401
-from test_low_tiles_cpu import LOADS_OF_A_BLOCK, launch_info
+from test_cpu_build import ADD, BALANCED, MUL, check, exe, launch_info, run_cpu  # noqa: F401
+from test_low_tiles_cpu import LOADS_OF_A_BLOCK
 
 LOADS_OF_HALF_A_WAVES_ROWS = 19 * 64
 

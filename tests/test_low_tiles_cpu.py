@@ -4,14 +4,9 @@ import numpy as np
 import pytest
 
 from paper_2509_25224_amd import workloads as wl
-from test_cpu_build import ADD, BALANCED, CAUSAL, COMP, MUL, check, exe, run_cpu  # noqa: F401
+from test_cpu_build import ADD, BALANCED, CAUSAL, COMP, MUL, check, exe, launch_info, run_cpu  # noqa: F401
 
 LOADS_OF_A_BLOCK = 64 * 72   # 16-byte loads
-
-
-def launch_info(tmp_path):
-    """Row tiles of a sequence, whether the balanced plan went by row tiles, direct-to-LDS loads, workgroups of run_cpu's last call."""
-    return (int(x) for x in np.fromfile(str(tmp_path / "out.bin.info"), np.int64, 4))
 
 
 @pytest.mark.parametrize("heads,columns,tile_rows,variant,flags", [(16, 5, 16, ADD, CAUSAL), (24, 5, 16, COMP, BALANCED),

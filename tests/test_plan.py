@@ -1,6 +1,7 @@
 """The balanced decomposition's integer arithmetic (csrc/amla_plan.h), run on the host through the
 C ABI (up to 256 workers, as many as a call can have, with the routines by which the kernels decide who owns which block;
-above that in exact integers)."""
+above that in exact integers): plans by sequence.  Which workers meet a sequence the merge of the transposed family derives from these; what the
+default family's workers note for theirs, and its plans by row tile, test_tile_plan_cpu.py reads."""
 import ctypes
 import os
 import subprocess
@@ -47,7 +48,7 @@ def test_pieces_tile_every_sequence_and_agree_with_the_combine_view(lens, worker
         assert at == nb[b]
         # a piece is full exactly when it is the sequence's only piece
         assert all(full == (len(runs) == 1) for _, _, _, full in runs)
-        # what the combine kernel derives: first and last worker, and every worker in between
+        # what the transposed family's merge derives: first and last worker, and every worker in between
         # that owns any block has a piece of this sequence
         if nb[b] == 0:
             assert tuple(seq_workers[b]) == (-1, -1)

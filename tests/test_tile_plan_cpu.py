@@ -5,8 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2509_25224_amd import workloads as wl
-from test_cpu_build import ADD, BALANCED, CAUSAL, COMP, MUL, check, exe, run_cpu  # noqa: F401
-from test_low_tiles_cpu import launch_info
+from test_cpu_build import ADD, BALANCED, CAUSAL, COMP, MUL, check, exe, launch_info, run_cpu  # noqa: F401
 
 
 @pytest.mark.parametrize("heads,s_q,lens,q_lens,workers,variant,flags,static,by_tile", [
