@@ -35,17 +35,19 @@
  *
  * Two kernel families run the path.  The default lays the accumulator out query row by register
  * (second product computed as O = P V): a register then belongs to two query rows, and the rescale
- * touches only the 16 registers of each row whose reference moved in the block.  It works a block as two
+ * touches only the 16 registers of each row whose reference moved in the block.  It works a block of 128 query rows as two
  * 32-key halves so that the softmax of one half runs under the MFMAs of the other; the reference follows
  * the running maximum once per 64-key block (MUL behind the second half, ADD behind the first; the other half
  * keeps the reference while no row has left it by more than 2^8) or per half (ADD_COMP).  The other
  * (AMLA_FLAG_TRANSPOSED_ACC) computes both products transposed, so the rescale factor is a per-lane
  * scalar and every rescale passes over all 256 accumulator registers of the wave; it is kept as the
  * baseline in which the cost of the paper's [V2] stage shows, and carries the lazy and ldexp forms.
- * The default runs sequences of at most 32 query rows (s_q * num_heads) in kernels of their own, in which
+ * The default runs row tiles of 16 and 32 query rows in kernels of their own, in which
  * all four waves of a workgroup work on a block: both products transposed, the value columns dealt among
  * the waves, a rescale over all 32 or 64 accumulator registers of a wave when one of its rows moved; the
- * reference follows the running maximum once per block, whichever variant.
+ * reference follows the running maximum once per block, whichever variant.  These take sequences of at most 32
+ * query rows (s_q * num_heads), and longer ones, in several tiles, in calls whose workgroups on such tiles all run
+ * at once, where the split factor or number of workers is the library's own (or the same number given).
  *
  * Every pointer below is a DEVICE pointer unless it says host.  amla_decode allocates no device
  * memory, never synchronises the device, reads no environment variable, and enqueues all work on
@@ -90,9 +92,14 @@ enum {
                                    ranges, one per worker workgroup; a worker walks its range sequence
                                    by sequence, and the pieces of a sequence are merged like split-KV
                                    partials.  desc->num_splits then means the number of workers
-                                   (0 = library chooses: one workgroup per compute unit), and the
-                                   workspace holds one slot per piece (amla_workspace_bytes answers for
-                                   this flag too).  Both kernel families. */
+                                   (0 = library chooses: one workgroup per compute unit, or for few
+                                   sequences fewer on lower row tiles), each with a workgroup for every
+                                   row tile, and the workspace holds one slot per piece
+                                   (amla_workspace_bytes answers for this flag too).  With desc->q_lens
+                                   the default kernels may lay out the blocks of all (sequence, row tile)
+                                   items that hold real tokens instead, and cut them into up to as many
+                                   ranges as there would be workgroups (256 at most).  Both kernel
+                                   families. */
   AMLA_FLAG_CAUSAL = 16,        /* causal mask among the s_q query tokens of a sequence (multi-token
                                    prediction: the s_q tokens are the last s_q positions of the cache):
                                    token t attends to keys 0 .. kv_len - s_q + t, i.e. to
@@ -107,8 +114,8 @@ enum {
                                    the reference the iteration started with (their weights may exceed 1;
                                    a row whose maximum leaves that reference by more than 2^8 moves it at
                                    once).  Counted from a range's first block, which sets the reference,
-                                   it moves in the last block of every eight, under ADD with more than 32
-                                   query rows a sequence in the first.  Same result up to rounding.  Default (row-rescale) kernels with
+                                   it moves in the last block of every eight, under ADD on row tiles of 128
+                                   in the first.  Same result up to rounding.  Default (row-rescale) kernels with
                                    AMLA_RESCALE_MUL or AMLA_RESCALE_ADD only. */
   AMLA_FLAG_TRANSPOSED_ACC = 128 /* run the kernels that compute both products transposed (S^T = K Q^T,
                                    O^T = V^T P^T): the accumulator's rescale factor is then a per-lane
@@ -132,7 +139,10 @@ typedef struct amla_desc {
   int32_t num_splits;          /* split-KV factor: each sequence's blocks are cut into this many
                                   contiguous ranges processed by separate workgroups and merged
                                   by a combine kernel.  0 = library chooses from the shape; at
-                                  most 256.  Either way a sequence is cut by the shape and its own
+                                  most 256.  The factor that it would choose, given here, is the same
+                                  call; with any other, sequences of more than 32 rows are worked in row
+                                  tiles of 128, in calls that leave compute units idle up to twice as
+                                  long as the library's own.  Either way a sequence is cut by the shape and its own
                                   length alone: its result does not depend on the batch's other
                                   lengths (under AMLA_FLAG_BALANCED it does, in the last bits). */
   int32_t flags;               /* AMLA_FLAG_* */
@@ -179,7 +189,7 @@ typedef struct amla_desc {
  *
  * Concurrency: the function may be called from several host threads; calls whose work may run at
  * the same time (different streams) need different `out`, `lse` and `desc->workspace` buffers.
- * The workspace need not be cleared between calls: every partial row that is read has been
+ * The workspace need not be cleared between calls: all that is read from it has been
  * written by the same call.
  */
 int amla_decode(const void* q, const void* kv_cache, const int32_t* block_table,
@@ -211,13 +221,13 @@ size_t amla_static_workspace_limit(void);
 /*
  * amla_workspace_bytes -- bytes of desc->workspace that amla_decode needs for this desc
  * (0 when the effective split factor is 1).  Only shape fields, num_splits and flags are
- * read.  Returns 0 for a NULL or unsupported desc.  The figure is 512 FP32 values and a log-sum-exp
- * per partial row whichever kernels run; the default kernels store their partial rows as FP16 (the
- * rows are normalised, so of the value rows' magnitude, and the merge weights them in FP32) and
- * leave the rest of the range untouched.  With the default kernels a sequence in several shares or
+ * read, and whether q_lens is given, which counts as AMLA_FLAG_BALANCED.  Returns 0 for a NULL or unsupported desc.  The figure is
+ * 512 FP32 values and a log-sum-exp per partial row whichever kernels run; the default kernels store their partial rows as FP16 (the
+ * rows are normalised, so of the value rows' magnitude, and the merge weights them in FP32), and the balanced ones use the rest
+ * for more of them and for notes on the plan: all of the range may be written.  With the default kernels a sequence in several shares or
  * pieces therefore needs averages of value rows within FP16's range: beyond 65504 they become
  * infinite, below 2^-14 they keep an absolute precision of 2^-25.  A call with a factor of 1
- * (amla_effective_splits) has BF16's range, and so have the transposed kernels, whose partial rows are
+ * (amla_effective_splits) has BF16's range (under ADD down to 2^-97, see above), and so have the transposed kernels, whose partial rows are
  * FP32; num_splits = 0 is a factor of 1 where a sequence can have at most nine blocks, except under
  * AMLA_FLAG_BALANCED.
  */
@@ -225,8 +235,8 @@ size_t amla_workspace_bytes(const amla_desc* desc);
 
 /*
  * amla_effective_splits -- the split-KV factor amla_decode will use for this desc
- * (desc->num_splits if > 0, else the library's choice from batch, rows and
- * max_blocks_per_seq).  Returns 0 for a NULL or unsupported desc.
+ * (desc->num_splits if > 0, else the library's choice from batch, rows,
+ * max_blocks_per_seq, flags and whether q_lens is given).  Returns 0 for a NULL or unsupported desc.
  */
 int amla_effective_splits(const amla_desc* desc);
 
@@ -258,13 +268,14 @@ int amla_mfma_probe(int32_t iters, int32_t workgroups, double* flops, void* stre
 int amla_device_info(int32_t* compute_units, int32_t* clock_khz);
 
 /*
- * amla_plan_segments -- host-only view of the balanced decomposition (AMLA_FLAG_BALANCED), computed
- * for up to 256 workers (as many as amla_decode has) with the routines the kernels use, above that in
- * 64-bit integers; for tests and for sizing.  `seqlens` is a HOST
+ * amla_plan_segments -- host-only view of the balanced decomposition (AMLA_FLAG_BALANCED) by sequence (not of plans by
+ * row tile, see there), computed for up to 256 workers (as many as amla_decode has) with the routines the kernels use, above that in
+ * 64-bit integers; for tests and for sizing.  Workers and slots are numbered as in the transposed family; the default one counts,
+ * where there are more workers than blocks, only those that have one.  `seqlens` is a HOST
  * array of `batch` lengths.  Writes up to `capacity` pieces as rows of six int32
  * (worker, sequence, first block, end block, workspace slot, covers-whole-sequence) to `pieces`
  * (host) in the order the workers produce them, the number of pieces to *n_pieces, and for every
- * sequence the first and last worker that meet it (as the combine kernel derives them; -1, -1 for
+ * sequence the first and last worker that meet it (as the transposed family's combine kernel derives them; -1, -1 for
  * an empty sequence) to seq_workers[2 * batch] (host).  Returns AMLA_ERR_WORKSPACE when
  * `capacity` was too small (*n_pieces is still the full count).
  */

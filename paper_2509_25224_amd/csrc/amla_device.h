@@ -204,7 +204,8 @@ __device__ __forceinline__ int lane_shift(int v) { return __builtin_amdgcn_updat
 // (ADD), by sequence / by tile: 40 sequences of 130 .. 5000 keys, three tokens, 2/3 of the pairs real 109.2 / 104.7, all of them 113.6 / 135.0; 64 of 3000 ..
 // 4000, four, 5/8 real 244.9 / 188.7; 100 of 100 .. 2000, two, 3/4 real 107.6 / 102.8; 200 of 64 .. 300, three, 2/3 real 95.5 / 97.5; 2 of three
 // tokens, one real, 1.3 units a worker 42.6 / 51.5.  Of 300 shapes of 1 .. 256 sequences, two to four row tiles and 3 .. 500 blocks no call that takes it is
-// more than 3 % slower than before there was a choice.
+// more than 3 % slower than before there was a choice (ADD; with ADD_COMP 17 of three tokens and 1536 keys 48.9 / 53.5: ranges by sequence that end
+// where sequences do).
 //   Tiles of 16 and 32 rows: ranges are shorter by a block and a half.  (The blocks and the merge take half as long, and no more workgroups than one round
 // holds are there to fill.)  60 sequences of two tokens of 64 heads, one real, 32.3 / 27.3; 3 of four of 128, up to two real, 30.8 / 23.1; 7 of three, two
 // real, 32.1 / 35.4.  Of 300 shapes 60 take it: 1.06 times as fast.
