@@ -200,12 +200,11 @@ __device__ __forceinline__ int lane_shift(int v) { return __builtin_amdgcn_updat
 // rows of real tokens, tile by tile, each range worked by one workgroup.  The second leaves no workgroup with padding tiles, but the tiles of a
 // sequence no longer share its blocks in an XCD's L2, and more results are merged.  So it is taken where a quarter of the (tile, block) pairs at
 // least are padding and the workers' ranges are long enough for that; every workgroup decides alike.
-//   Tiles of 128 rows: sequences have eight blocks on average, workers two units, or one and a half where that is two less than by sequence.  us a call
-// (ADD), by sequence / by tile: 40 sequences of 130 .. 5000 keys, three tokens, 2/3 of the pairs real 109.2 / 104.7, all of them 113.6 / 135.0; 64 of 3000 ..
-// 4000, four, 5/8 real 244.9 / 188.7; 100 of 100 .. 2000, two, 3/4 real 107.6 / 102.8; 200 of 64 .. 300, three, 2/3 real 95.5 / 97.5; 2 of three
-// tokens, one real, 1.3 units a worker 42.6 / 51.5.  Of 300 shapes of 1 .. 256 sequences, two to four row tiles and 3 .. 500 blocks no call that takes it is
-// more than 3 % slower than before there was a choice (ADD; with ADD_COMP 17 of three tokens and 1536 keys 48.9 / 53.5: ranges by sequence that end
-// where sequences do).
+//   Tiles of 128 rows: ranges are shorter by 0.6 blocks and 0.05 for every further piece that an item then has in the merge.  us a call (ADD), by sequence / by
+// tile: 40 sequences of 130 .. 5000 keys, three tokens, 2/3 of the pairs real 109.2 / 104.7, all of them 113.6 / 135.0; 64 of 3000 .. 4000, four, 5/8 real
+// 244.9 / 188.7; 100 of 100 .. 2000, two, 3/4 real 107.6 / 102.8; 17 of four, one real 189.9 / 90.1; 2 of three, one real, 85 more pieces for 2.7 blocks 42.6 /
+// 51.5.  Of 743 shapes of 1 .. 256 sequences, two to four row tiles and 3 .. 500 blocks 285 take it: 1.21 times as fast, seven of them more than 3 % slower (at
+// worst 40.3 / 46.5 and 85 / 97; 17 of three tokens and 24 blocks each 48.9 / 53.5, ADD_COMP: ranges by sequence end where the sequences do).
 //   Tiles of 16 and 32 rows: ranges are shorter by a block and a half.  (The blocks and the merge take half as long, and no more workgroups than one round
 // holds are there to fill.)  60 sequences of two tokens of 64 heads, one real, 32.3 / 27.3; 3 of four of 128, up to two real, 30.8 / 23.1; 7 of three, two
 // real, 32.1 / 35.4.  Of 300 shapes 60 take it: 1.06 times as fast.

@@ -1,5 +1,5 @@
 """Per-sequence token counts in the CPU build (see test_cpu_build.py): the balanced plan goes by row tiles where a quarter of the (tile, block) pairs are
-padding, sequences have eight blocks on average and workers two units, else by sequences; the workspace of exactly the documented size holds either one's pieces
+padding and that makes the workers' ranges enough shorter, else by sequences; the workspace of exactly the documented size holds either one's pieces
 and notes."""
 import numpy as np
 import pytest
@@ -9,15 +9,16 @@ from test_cpu_build import ADD, BALANCED, CAUSAL, COMP, MUL, check, exe, launch_
 
 
 @pytest.mark.parametrize("heads,s_q,lens,q_lens,workers,variant,flags,static,by_tile", [
-    (65, 2, [700, 64, 1000, 580], [1, 2, 2, 0], 1, ADD, CAUSAL, False, True),     # two tiles, the last of two rows; one worker a tile
+    (65, 2, [700, 64, 1000, 580], [1, 2, 2, 0], 2, ADD, CAUSAL, False, True),     # two tiles, the last of two rows
+    (65, 2, [700, 64, 1000, 580], [1, 2, 2, 0], 1, ADD, CAUSAL, False, False),    # a workspace with slots for one worker by tile
     (65, 2, [700, 64, 1000, 580], [1, 2, 2, 0], 40, MUL, CAUSAL, True, False),    # more workers than units
-    (65, 2, [700, 0, 520, 580], [1, 2, 2, 0], 1, COMP, CAUSAL, False, False),     # 30 blocks of four sequences
+    (65, 2, [700, 0, 520, 580], [1, 2, 2, 0], 1, COMP, CAUSAL, False, True),      # one of them empty
     (129, 1, [1200, 513], [0, 1], 3, COMP, BALANCED, False, True),                # a tile of one row; a sequence of many keys without tokens
     (128, 2, [512, 511], [1, 2], 2, ADD, CAUSAL, False, True),                    # 24 of 32 pairs
-    (128, 2, [512, 511], [1, 2], 6, ADD, CAUSAL, True, True),                     # two units for each of twelve workers
-    (128, 2, [512, 511], [1, 2], 7, MUL, CAUSAL, False, False),                   # less
+    (128, 2, [512, 511], [1, 2], 6, ADD, CAUSAL, True, True),                     # two units for 2.67 blocks, one piece more
+    (128, 2, [512, 511], [1, 2], 7, MUL, CAUSAL, False, False),                   # 1.71 for 2.29, 1.17 more
     (128, 2, [576, 512], [2, 1], 2, ADD, CAUSAL, False, False),                   # 26 of 34 pairs
-    (128, 2, [512, 448], [1, 1], 2, ADD, CAUSAL, False, False),                   # 15 blocks of two sequences
+    (128, 2, [512, 448], [1, 1], 2, ADD, CAUSAL, False, True),                    # half of them
     (129, 1, [600], [1], 1, MUL, BALANCED, False, False)])                        # the smallest workspace of two tiles: two slots' worth
 def test_plans_by_tile_and_by_sequence(exe, tmp_path, heads, s_q, lens, q_lens, workers, variant, flags, static, by_tile):
     case = wl.make_case("tile_plan", 103, batch=len(lens), s_q=s_q, heads=heads, seqlens=lens, spare_frac=0.2)
