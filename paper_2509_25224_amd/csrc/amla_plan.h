@@ -3,8 +3,9 @@
 // ranges of equal length.  A worker walks its range sequence by sequence; every (worker, sequence)
 // pair it touches is a *piece* with its own softmax state, and pieces of one sequence are merged
 // afterwards exactly like split-KV partials (the merge rule of Algorithm 1's update).  This file
-// holds the arithmetic shared by the decode kernel, the combine kernel and the host-side
-// test entry point, so that all three agree on who owns which block and which slot.
+// holds the arithmetic shared by the decode kernels, the transposed family's combine kernel and the host-side
+// test entry point, so that all agree on who owns which block and which slot.  (The default family's
+// workers note what its combine kernel has to know, and may lay row tiles end to end: PlanUnits.)
 //
 // Facts used by the callers (checked by the CPU tests through amla_plan_segments):
 //   * worker w owns global blocks [plan_worker_begin(w), plan_worker_begin(w + 1));

@@ -8,6 +8,22 @@ from paper_2509_25224_amd import workloads as wl
 from test_cpu_build import ADD, BALANCED, CAUSAL, COMP, MUL, check, exe, launch_info, run_cpu  # noqa: F401
 
 
+@pytest.mark.parametrize("heads,s_q,lens,q_lens,workers,variant,flags,static", [
+    (65, 2, [700, 0, 520, 580], [1, 2, 2, 0], 1, ADD, CAUSAL, False),      # two tiles, the last of two rows; one worker a tile, one empty sequence
+    (65, 2, [700, 0, 520, 580], [1, 2, 2, 0], 40, MUL, CAUSAL, True),      # more workers than units
+    (129, 1, [1200, 513], [0, 1], 3, COMP, BALANCED, False),               # a tile of one row; a sequence of many keys without tokens
+    (128, 2, [512, 511], [1, 2], 2, ADD, CAUSAL, False),                   # 24 of 32 pairs
+    (128, 2, [576, 512], [2, 1], 2, ADD, CAUSAL, False),                   # 26 of 34
+    (128, 2, [512, 448], [1, 1], 2, ADD, CAUSAL, False),                   # half of them
+    (129, 1, [600], [1], 1, MUL, BALANCED, False)])                        # the smallest workspace of two tiles: two slots' worth
+def test_plans_by_tile_and_by_sequence(exe, tmp_path, heads, s_q, lens, q_lens, workers, variant, flags, static):
+    case = wl.make_case("tile_plan", 103, batch=len(lens), s_q=s_q, heads=heads, seqlens=lens, spare_frac=0.2)
+    out, lse, _ = run_cpu(exe, tmp_path, case, variant, flags=flags, ns=workers, q_lens=q_lens, static_ws=static)
+    check(out, lse, case, causal=bool(flags & CAUSAL), q_lens=q_lens)
+    for b, k in enumerate(q_lens):
+        assert np.all(out[b, k:] == 0) and np.all(np.isneginf(lse[b, k:]))
+
+
 @pytest.mark.parametrize("heads,s_q,lens,q_lens,workers,variant,flags,static,by_tile", [
     (65, 2, [700, 64, 1000, 580], [1, 2, 2, 0], 2, ADD, CAUSAL, False, True),     # two tiles, the last of two rows
     (65, 2, [700, 64, 1000, 580], [1, 2, 2, 0], 1, ADD, CAUSAL, False, False),    # a workspace with slots for one worker by tile
@@ -20,7 +36,7 @@ from test_cpu_build import ADD, BALANCED, CAUSAL, COMP, MUL, check, exe, launch_
     (128, 2, [576, 512], [2, 1], 2, ADD, CAUSAL, False, False),                   # 26 of 34 pairs
     (128, 2, [512, 448], [1, 1], 2, ADD, CAUSAL, False, True),                    # half of them
     (129, 1, [600], [1], 1, MUL, BALANCED, False, False)])                        # the smallest workspace of two tiles: two slots' worth
-def test_plans_by_tile_and_by_sequence(exe, tmp_path, heads, s_q, lens, q_lens, workers, variant, flags, static, by_tile):
+def test_which_plan_is_taken(exe, tmp_path, heads, s_q, lens, q_lens, workers, variant, flags, static, by_tile):
     case = wl.make_case("tile_plan", 103, batch=len(lens), s_q=s_q, heads=heads, seqlens=lens, spare_frac=0.2)
     out, lse, _ = run_cpu(exe, tmp_path, case, variant, flags=flags, ns=workers, q_lens=q_lens, static_ws=static)
     check(out, lse, case, causal=bool(flags & CAUSAL), q_lens=q_lens)
